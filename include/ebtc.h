@@ -134,16 +134,16 @@ enum ebtc_spmv_form {
                                 stay whole, so the sums are the stream form's; for graphs whose
                                 first rows hold most entries (preferential attachment). Each call
                                 first finds every share's rows                                     */
-  EBTC_SPMV_PANELED = 6      /* for vectors too large for the column-segmented form: each call first
-                                puts the entries of groups of row units (64-256 rows) in column-panel
-                                order (seg_len columns per panel, 0 = 12288 FP32 / 6144 FP64); each
-                                step then forms the products panel by panel, one vector slice in LDS
-                                serving a group's entries, and a second pass sums every row's products
-                                in entry order (the stream form's sums, bit for bit). Units with more
-                                entries than the row-sum pass holds in LDS (1.5 times the densest
-                                realization's mean per unit, at most 32768 FP32 / 16384 FP64) or a row
-                                beyond the stream form's LDS capacity use the CSR-stream arithmetic;
-                                at most 1024 panels per realization                                */
+  EBTC_SPMV_PANELED = 6      /* each call first cuts every realization's rows into shares that fill a
+                                workgroup's LDS with their FP64 sums and sorts each share's entries by
+                                column panel (seg_len columns per panel asked for, 0 = 12288 FP32 /
+                                6144 FP64; the kernels take at most 8192 / 4096); each step then stages
+                                one panel's vector slice at a time in LDS, gathers from it and adds
+                                every product to its row's sum in entry order (the stream form's sums,
+                                bit for bit). Long rows (more than 256 entries and six times the mean)
+                                are summed apart; a share with columns out of order uses the CSR-stream
+                                arithmetic; at most 1024 panels of the columns asked for per
+                                realization                                                          */
 };
 #define EBTC_TUNE_SLOTS 10 /* entries of ebtc_tune's ms_out */
 
@@ -291,8 +291,9 @@ int ebtc_subgraph_centrality(int32_t dtype, int32_t n, const int32_t* row_ptr, c
  * segments, the column-segmented form with 6144 and 12288 FP32 (3072 and 6144 FP64) columns when at
  * most 32 segments, the entry-balanced and the paneled form; each form whose plan fits ws_bytes gets
  * its once-per-call preparation, one warm-up and three timed launches of the first Lanczos product.
- * The fastest per launch, with its preparation spread over the call's m steps, is recorded in the
- * cache under the composition and in the batch; later calls with opts->spmv == EBTC_SPMV_AUTO use it
+ * The fastest per launch, with its preparation spread over the call's m steps (adaptive: 16; the
+ * paneled form only in the place of a form with its sums: stream, column-segmented or
+ * entry-balanced), is recorded in the cache under the composition and in the batch; later calls with opts->spmv == EBTC_SPMV_AUTO use it
  * (a form named in opts overrides it). Plan the later calls after tuning: the chosen form sets their
  * workspace size. Synchronous on the stream. Overwrites the workspace (the largest ebtc_plan size over
  * the forms to try, 256-byte aligned; forms whose plan does not fit are skipped); not thread-safe with

@@ -47,20 +47,17 @@ struct FormLayout {
   // entry-balanced SpMV arenas
   size_t off_bal = 0, off_balbeg = 0;
   int64_t nbal = 0;  // shares over the form's realizations
-  // panel-form arenas
-  size_t off_panflag = 0, off_panrun = 0, off_pancol = 0, off_panperm = 0, off_panval = 0, off_panprod = 0,
-         off_panitems = 0, off_pangroups = 0;
-  int64_t npan_items = 0, npan_groups = 0;
+  // paneled-form arenas
+  size_t off_tilebeg = 0, off_tilecut = 0, off_tilencut = 0, off_tileshare = 0, off_tilebase = 0, off_tileend = 0,
+         off_tileent = 0, off_tileval = 0, off_tilecnt = 0, off_hubrow = 0, off_hubbatch = 0;
+  int64_t ntile = 0;
 };
 
 // Host tables of one SpMV form (uploaded with every call; kept in the batch for the async copies).
 struct FormHost {
   std::vector<int32_t> sub;          // [blocks] the form's row blocks, batch-wide ids (mixed plans only)
   std::vector<int64_t> bal_begin;    // [R + 1] first entry-balanced share of each realization (0 elsewhere)
-  std::vector<PanItem> pan_items;    // products-pass work items, realization by realization
-  std::vector<int64_t> pan_begin;    // [R + 1] first work item of each realization
-  std::vector<PanItem> pan_groups;   // unit groups of the sort's scan, realization by realization
-  std::vector<int64_t> pan_gbegin;   // [R + 1] first group of each realization
+  std::vector<int64_t> tile_begin;   // [R + 1] first paneled share slot of each realization
 };
 
 struct Layout {
@@ -166,15 +163,16 @@ struct SpmvPlan {
   int segcols = 0;  // column-segmented: columns per segment
   int smax = 0;     // column-segmented: segments of the largest realization
   int balent = 0;   // entry-balanced: entries per share
-  int pancols = 0;  // paneled: columns per panel
-  int pmax = 0;     // paneled: panels of the largest realization
-  int panunit = 0;  // paneled: rows per unit
-  int panlds = 0;   // paneled: entries of a unit held by the row-sum pass
+  int pancols = 0;   // paneled: columns per panel
+  int panask = 0;    // paneled: columns per panel asked for (the limit of 1024 panels counts these)
+  int pmax = 0;      // paneled: panels of the largest realization
+  int tilerows = 0;  // paneled: rows per share
+  int tileshort = 0;  // paneled: a band's runs of entries per panel are short
   // the parameter ebtc_opts::seg_len carries for this form
   int param() const {
     return form == EBTC_SPMV_SEGMENTED ? segcols
            : form == EBTC_SPMV_BALANCED ? balent
-           : form == EBTC_SPMV_PANELED  ? pancols
+           : form == EBTC_SPMV_PANELED  ? panask
                                         : seglen;
   }
 };
@@ -192,7 +190,7 @@ struct BatchPlan {
       t += std::to_string(p.form) + "," + std::to_string(p.lanes) + "," + std::to_string(p.hub) + "," +
            std::to_string(p.seglen) + "," + std::to_string(p.segcols) + "," + std::to_string(p.smax) + "," +
            std::to_string(p.balent) + "," + std::to_string(p.pancols) + "," + std::to_string(p.pmax) + "," +
-           std::to_string(p.panunit) + "," + std::to_string(p.panlds) + ";";
+           std::to_string(p.tilerows) + "," + std::to_string(p.tileshort) + ";";
     if (mixed())
       for (int32_t f : graph_form) t += std::to_string(f) + ",";
     return t;
@@ -204,6 +202,12 @@ using Members = std::vector<char>;
 bool member(const Members* m, int32_t g) { return m == nullptr || (*m)[g] != 0; }
 
 std::vector<int64_t> bal_shares(const ebtc_batch* b, int e, const Members* m);
+std::vector<int64_t> tile_begins(const ebtc_batch* b, int rows, const Members* m);
+
+// Panels per realization at the columns asked for, and the widest panel that may be asked for (the kernels
+// take narrower ones where these exceed their slice buffers).
+constexpr int kPanelLimit = 1024;
+int panel_ask(int dtype) { return dtype == EBTC_F64 ? 6144 : 12288; }
 
 int check_form(const ebtc_batch* b, const SpmvPlan& p, const Members* m) {
   if (p.form == EBTC_SPMV_LANE_GROUPS && p.lanes != 4 && p.lanes != 8 && p.lanes != 16 && p.lanes != 32)
@@ -213,10 +217,16 @@ int check_form(const ebtc_batch* b, const SpmvPlan& p, const Members* m) {
       return fail(EBTC_EINVAL, "the entry-balanced SpMV takes shares of 256 to 2^24 entries (seg_len)");
     if (bal_shares(b, p.balent, m).back() > INT32_MAX) return fail(EBTC_EINVAL, "too many entry-balanced shares");
   }
-  if (p.form == EBTC_SPMV_PANELED && p.pmax > kPanMaxPanels)
-    return fail(EBTC_EINVAL, "the paneled SpMV takes at most " + std::to_string(kPanMaxPanels) + " panels: n " +
-                                 std::to_string(p.pmax * (int64_t)p.pancols) + " > " + std::to_string(kPanMaxPanels) +
-                                 " x " + std::to_string(p.pancols));
+  if (p.form == EBTC_SPMV_PANELED) {
+    int32_t n_max = 1;
+    for (int32_t g = 0; g < b->G; ++g)
+      if (member(m, g)) n_max = std::max(n_max, b->n[g]);
+    if ((n_max + (int64_t)p.panask - 1) / p.panask > kPanelLimit)
+      return fail(EBTC_EINVAL, "the paneled SpMV takes at most " + std::to_string(kPanelLimit) + " panels: n " +
+                                   std::to_string(n_max) + " > " + std::to_string(kPanelLimit) + " x " +
+                                   std::to_string(p.panask));
+    if (tile_begins(b, p.tilerows, m).back() > kTileMaxSlots) return fail(EBTC_EINVAL, "too many paneled shares");
+  }
   if (p.form == EBTC_SPMV_SEGMENTED && p.smax > kSegMax)
     return fail(EBTC_EINVAL, "the column-segmented SpMV needs at most " + std::to_string(kSegMax) +
                                  " segments: n " + std::to_string(p.smax * (int64_t)p.segcols) + " > " +
@@ -271,45 +281,37 @@ int bal_default(const ebtc_batch* b, const Members* m) {
   return e;
 }
 
-// The panel form's unit groups and products-pass work items: per member realization, groups of units
-// sized so that staging a panel's slice costs at most about a tenth of the product traffic of the
-// group's run of that panel (2 + 2 s bytes per entry: column, value, product), halved while the form
-// has fewer than 1536 items; items panel by panel, group by group.
-void pan_tables(const ebtc_batch* b, int S, int U, const Members* m, FormHost& h) {
-  const double es = elem_size(b->dtype);
-  auto build = [&](int shrink) {
-    h.pan_items.clear();
-    h.pan_groups.clear();
-    h.pan_begin.assign((size_t)b->R + 1, 0);
-    h.pan_gbegin.assign((size_t)b->R + 1, 0);
-    int64_t r = 0;
-    for (int32_t g = 0; g < b->G; ++g) {
-      const int32_t nr = b->n[g];
-      const int units = (nr + U - 1) / U, P = (nr + S - 1) / S;
-      for (int32_t k = 0; k < b->nreal[g]; ++k, ++r) {
-        if (member(m, g)) {
-          const double per = std::max(1.0, (double)b->nnz_r[r] / ((double)units * P));  // entries per (unit, panel)
-          int gsz = (int)std::ceil(10.0 * S * es / ((2.0 + 2.0 * es) * per));
-          gsz = std::max(1, std::min(units, gsz >> shrink));
-          const size_t g0 = h.pan_groups.size();
-          for (int u0 = 0; u0 < units; u0 += gsz) h.pan_groups.push_back({(int32_t)r, 0, u0, std::min(units, u0 + gsz)});
-          for (int p = 0; p < P; ++p)
-            for (size_t q = g0; q < h.pan_groups.size(); ++q)
-              h.pan_items.push_back({(int32_t)r, p, h.pan_groups[q].b0, h.pan_groups[q].b1});
-        }
-        h.pan_begin[r + 1] = (int64_t)h.pan_items.size();
-        h.pan_gbegin[r + 1] = (int64_t)h.pan_groups.size();
-      }
-    }
+// First paneled share slot of each realization ([R + 1]; none for realizations of other forms). rows: what
+// tile_rows chose; the shares may take fewer (tile_min_rows).
+std::vector<int64_t> tile_begins(const ebtc_batch* b, int rows, const Members* m) {
+  std::vector<int64_t> v((size_t)b->R + 1, 0);
+  int64_t full = 0, r = 0;
+  for (int32_t g = 0; g < b->G; ++g)
+    if (member(m, g)) full += ((int64_t)b->n[g] + rows - 1) / rows * b->nreal[g];
+  const int least = tile_min_rows(rows, (int)std::min<int64_t>(1 << 20, std::max<int64_t>(1, (full + kTileUnits - 1) / kTileUnits)));
+  for (int32_t g = 0; g < b->G; ++g)
+    for (int32_t k = 0; k < b->nreal[g]; ++k, ++r)
+      v[r + 1] = v[r] + (member(m, g) ? tile_slots(least, b->n[g], b->nnz_r[r]) : 0);
+  return v;
+}
+
+// Rows per share of the paneled form: a compute unit holds one share at a time, so as few rounds of 256
+// shares as the largest share allows, filled as well as they can be (64 x n=1e5: 3 rounds of 256 shares
+// of 8334 rows; with 12160 rows the same three rounds would be 2.25 full).
+int tile_rows(const ebtc_batch* b, const Members* m) {
+  auto shares = [&](int64_t rows) {
+    int64_t t = 0;
+    for (int32_t g = 0; g < b->G; ++g)
+      if (member(m, g)) t += (b->n[g] + rows - 1) / rows * b->nreal[g];
+    return t;
   };
-  int shrink = 0;
-  build(shrink);
-  while (h.pan_items.size() < 1536 && shrink < 16) {
-    ++shrink;
-    const size_t before = h.pan_items.size();
-    build(shrink);
-    if (h.pan_items.size() == before) break;
+  const int64_t target = (shares(kTileMaxRows) + kTileUnits - 1) / kTileUnits * kTileUnits;
+  int lo = kTileMinRows, hi = kTileMaxRows;  // the fewest rows whose shares do not exceed the rounds
+  while (lo < hi) {
+    const int mid = (lo + hi) / 2;
+    if (shares(mid) <= target) hi = mid; else lo = mid + 1;
   }
+  return lo;
 }
 
 // The batch's host tables for plan bp (rebuilt when the plan changes).
@@ -334,7 +336,7 @@ const std::vector<FormHost>& form_host(const ebtc_batch* cb, const BatchPlan& bp
       }
     }
     if (p.form == EBTC_SPMV_BALANCED) h.bal_begin = bal_shares(b, p.balent, mp);
-    if (p.form == EBTC_SPMV_PANELED) pan_tables(b, p.pancols, p.panunit, mp, h);
+    if (p.form == EBTC_SPMV_PANELED) h.tile_begin = tile_begins(b, p.tilerows, mp);
   }
   b->fh_sig = sig;
   return b->fh;
@@ -410,25 +412,24 @@ Layout make_layout(const ebtc_batch* b, const ebtc_opts* o, const BatchPlan& bp)
       if (b->values) off = align_up(off + es * slots);
     }
     if (sp.form == EBTC_SPMV_PANELED) {
-      const int64_t units = F.blocks * (kRowsPerBlock / sp.panunit);
-      F.npan_items = (int64_t)fh[f].pan_items.size();
-      F.npan_groups = (int64_t)fh[f].pan_groups.size();
-      F.off_panflag = off;
-      off = align_up(off + sizeof(int32_t) * (size_t)units);
-      F.off_panrun = off;
-      off = align_up(off + sizeof(int2) * (size_t)sp.pmax * (size_t)units);
-      F.off_pancol = off;
-      off = align_up(off + sizeof(uint16_t) * z);
-      F.off_panperm = off;
-      off = align_up(off + sizeof(uint16_t) * z);
-      F.off_panval = off;
-      if (b->values) off = align_up(off + es * z);
-      F.off_panprod = off;
-      off = align_up(off + es * z);
-      F.off_panitems = off;
-      off = align_up(off + sizeof(PanItem) * (size_t)F.npan_items);
-      F.off_pangroups = off;
-      off = align_up(off + sizeof(PanItem) * (size_t)F.npan_groups);
+      F.ntile = fh[f].tile_begin.back();
+      const size_t slots = (size_t)F.ntile, places = (slots + 7) / 8 * 8, hubs = (size_t)tile_hub_rows(F.z);
+      auto take = [&](size_t bytes) {
+        const size_t o = off;
+        off = align_up(off + bytes);
+        return o;
+      };
+      F.off_tilebeg = take(sizeof(int64_t) * (size_t)(b->R + 1));
+      F.off_tilecut = take(sizeof(TileCut) * slots);
+      F.off_tilencut = take(sizeof(int32_t) * (size_t)(b->R + 1));
+      F.off_tileshare = take(sizeof(TileShare) * places);
+      F.off_tilebase = take(sizeof(int64_t) * kTileBandsHost * places);
+      F.off_tileend = take(sizeof(uint32_t) * kTileBandsHost * (size_t)sp.pmax * places);
+      F.off_tileent = take(sizeof(uint32_t) * z);
+      if (b->values) F.off_tileval = take(es * z);
+      F.off_tilecnt = take(sizeof(int32_t) * 4);
+      F.off_hubrow = take(sizeof(int32_t) * hubs);
+      F.off_hubbatch = take(sizeof(HubBatch) * hubs);
     }
     if (sp.form == EBTC_SPMV_BALANCED) {
       F.nbal = fh[f].bal_begin.back();
@@ -491,12 +492,9 @@ int upload_tables(ebtc_batch* b, char* ws, const Layout& L, const BatchPlan& bp,
     if (bp.mixed() && F.blocks > 0)
       EBTC_HIP(hipMemcpyAsync(ws + F.off_sub, fh[f].sub.data(), sizeof(int32_t) * (size_t)F.blocks,
                               hipMemcpyHostToDevice, s));
-    if (F.npan_items > 0) {
-      EBTC_HIP(hipMemcpyAsync(ws + F.off_panitems, fh[f].pan_items.data(), sizeof(PanItem) * (size_t)F.npan_items,
+    if (bp.forms[f].form == EBTC_SPMV_PANELED)
+      EBTC_HIP(hipMemcpyAsync(ws + F.off_tilebeg, fh[f].tile_begin.data(), sizeof(int64_t) * (b->R + 1),
                               hipMemcpyHostToDevice, s));
-      EBTC_HIP(hipMemcpyAsync(ws + F.off_pangroups, fh[f].pan_groups.data(),
-                              sizeof(PanItem) * (size_t)F.npan_groups, hipMemcpyHostToDevice, s));
-    }
     if (bp.forms[f].form == EBTC_SPMV_BALANCED)
       EBTC_HIP(hipMemcpyAsync(ws + F.off_balbeg, fh[f].bal_begin.data(), sizeof(int64_t) * (b->R + 1),
                               hipMemcpyHostToDevice, s));
@@ -509,16 +507,8 @@ SpmvPlan spmv_form(const ebtc_batch* b, int form, int lanes, int seg_len, int hu
   SpmvPlan p;
   p.form = form;
   int32_t n_max = 1;
-  double deg = 0.0;  // the densest member realization's mean degree
-  {
-    int64_t r = 0;
-    for (int32_t g = 0; g < b->G; ++g)
-      for (int32_t k = 0; k < b->nreal[g]; ++k, ++r)
-        if (member(m, g)) {
-          n_max = std::max(n_max, b->n[g]);
-          deg = std::max(deg, (double)b->nnz_r[r] / std::max(1, b->n[g]));
-        }
-  }
+  for (int32_t g = 0; g < b->G; ++g)
+    if (member(m, g)) n_max = std::max(n_max, b->n[g]);
   if (form == EBTC_SPMV_LANE_GROUPS) p.lanes = lanes ? lanes : 8;
   if (form == EBTC_SPMV_LDS_STAGED) {
     const int maxseg = staged_max_seglen(b->dtype);
@@ -530,16 +520,21 @@ SpmvPlan spmv_form(const ebtc_batch* b, int form, int lanes, int seg_len, int hu
   }
   if (form == EBTC_SPMV_BALANCED) p.balent = seg_len > 0 ? seg_len : bal_default(b, m);
   if (form == EBTC_SPMV_PANELED) {
-    p.pancols = std::min(seg_len > 0 ? seg_len : pan_max_cols(b->dtype), pan_max_cols(b->dtype));
+    p.panask = std::min(seg_len > 0 ? seg_len : panel_ask(b->dtype), panel_ask(b->dtype));
+    p.pancols = std::min(p.panask, tile_max_cols(b->dtype));
     p.pmax = (n_max + p.pancols - 1) / p.pancols;
-    // units: the most rows (256, 128 or 64) whose entries, at 1.5 times the densest realization's mean
-    // degree, fit the stream arithmetic's LDS buffer, which the row-sum pass holds anyway; the budget
-    // is that buffer, or 1.5 times a 64-row unit's mean entries when even those do not fit
-    const int cap = stream_cap(b->dtype);
-    p.panunit = 256;
-    while (p.panunit > 64 && p.panunit * deg * 1.5 > cap) p.panunit >>= 1;
-    const double need = std::ceil(p.panunit * deg * 1.5 / 256.0) * 256.0;
-    p.panlds = (int)std::min<double>(pan_max_lds(b->dtype), std::max<double>(cap, need));
+    p.tilerows = tile_rows(b, m);
+    // entries of a band in a panel, over all member realizations: chunks of 384 pay above about 128
+    double z = 0.0, runs = 0.0;
+    int64_t r = 0;
+    for (int32_t g = 0; g < b->G; ++g)
+      for (int32_t k = 0; k < b->nreal[g]; ++k, ++r)
+        if (member(m, g)) {
+          z += (double)b->nnz_r[r];
+          runs += (double)((b->n[g] + p.tilerows - 1) / p.tilerows) * kTileBandsHost *
+                  ((b->n[g] + p.pancols - 1) / p.pancols);
+        }
+    p.tileshort = z < 128.0 * runs ? 1 : 0;
   }
   p.hub = hub ? hub : 16 * (p.lanes ? p.lanes : 8);
   return p;
@@ -612,8 +607,9 @@ std::vector<FArgs> form_args(const ebtc_batch* b, const LzArgs& base, char* ws, 
     a.sub_blocks = bp.mixed() ? (const int32_t*)(ws + F.off_sub) : nullptr;
     a.hub_threshold = sp.hub;
     a.seglen = sp.seglen;
-    // the column-segmented sort of weighted graphs also writes step 0's product
-    a.first_in_prepare = base.unit_start && sp.form == EBTC_SPMV_SEGMENTED && b->values != nullptr ? 1 : 0;
+    // the column-segmented and the paneled sort of weighted graphs also write step 0's product
+    const bool sorted = sp.form == EBTC_SPMV_SEGMENTED || sp.form == EBTC_SPMV_PANELED;
+    a.first_in_prepare = base.unit_start && sorted && b->values != nullptr ? 1 : 0;
     if (sp.form == EBTC_SPMV_SEGMENTED) {
       a.seg_cols = sp.segcols;
       a.seg_stride = sp.smax * kRowsPerBlock;
@@ -635,17 +631,20 @@ std::vector<FArgs> form_args(const ebtc_batch* b, const LzArgs& base, char* ws, 
     if (sp.form == EBTC_SPMV_PANELED) {
       a.pan_cols = sp.pancols;
       a.pan_pmax = sp.pmax;
-      a.pan_unit = sp.panunit;
-      a.pan_lds = sp.panlds;
-      a.pan_flag = (int32_t*)(ws + F.off_panflag);
-      a.pan_run = (int2*)(ws + F.off_panrun);
-      a.pan_col = (uint16_t*)(ws + F.off_pancol);
-      a.pan_perm = (uint16_t*)(ws + F.off_panperm);
-      a.pan_val = b->values ? (void*)(ws + F.off_panval) : nullptr;
-      a.pan_prod = ws + F.off_panprod;
-      a.pan_items = (const PanItem*)(ws + F.off_panitems);
-      a.pan_nitems = (int32_t)F.npan_items;
-      a.pan_groups = (const PanItem*)(ws + F.off_pangroups);
+      a.tile_rows = sp.tilerows;
+      a.ntile = (int32_t)F.ntile;
+      a.tile_begin = (const int64_t*)(ws + F.off_tilebeg);
+      a.tile_cut = (TileCut*)(ws + F.off_tilecut);
+      a.tile_ncut = (int32_t*)(ws + F.off_tilencut);
+      a.tile_share = (TileShare*)(ws + F.off_tileshare);
+      a.tile_base = (int64_t*)(ws + F.off_tilebase);
+      a.tile_short = sp.tileshort;
+      a.tile_end = (uint32_t*)(ws + F.off_tileend);
+      a.tile_ent = (uint32_t*)(ws + F.off_tileent);
+      a.tile_val = b->values ? (void*)(ws + F.off_tileval) : nullptr;
+      a.tile_count = (int32_t*)(ws + F.off_tilecnt);
+      a.hub_row = (int32_t*)(ws + F.off_hubrow);
+      a.hub_batch = (HubBatch*)(ws + F.off_hubbatch);
     }
     if (sp.form == EBTC_SPMV_BALANCED) {
       a.bal = (BalPart*)(ws + F.off_bal);
@@ -667,10 +666,7 @@ FArgs one_task(const ebtc_batch* b, const FArgs& x, size_t f, int64_t r) {
   y.nb = b->tasks[r].nblk;
   const FormHost& h = b->fh[f];
   if (y.a.bal != nullptr) y.a.nbal = (int32_t)(h.bal_begin[r + 1] - h.bal_begin[r]);
-  if (y.a.pan_cols > 0) {
-    y.a.pan_items = x.a.pan_items + h.pan_begin[r];
-    y.a.pan_nitems = (int32_t)(h.pan_begin[r + 1] - h.pan_begin[r]);
-  }
+  if (y.a.pan_cols > 0) y.a.ntile = (int32_t)(h.tile_begin[r + 1] - h.tile_begin[r]);
   return y;
 }
 
@@ -695,7 +691,7 @@ int prepare_kernels(const BatchPlan& bp) {
   for (const SpmvPlan& sp : bp.forms) {
     if (sp.seglen > 0) EBTC_HIP(prepare_staged_kernels());
     if (sp.segcols > 0) EBTC_HIP(prepare_seg_kernels());
-    if (sp.pancols > 0) EBTC_HIP(prepare_pan_kernels());
+    if (sp.pancols > 0) EBTC_HIP(prepare_tile_kernels());
   }
   EBTC_HIP(prepare_solve_kernels());
   return EBTC_OK;
@@ -802,12 +798,9 @@ int enqueue_prepare(const ebtc_batch* b, const FArgs& x, size_t f, hipStream_t s
     return EBTC_OK;
   }
   if (x.sp.form == EBTC_SPMV_PANELED) {
-    const FormHost& h = b->fh[f];
     const bool one = a.blkmap == nullptr;
-    const int64_t g0 = one ? h.pan_gbegin[a.single_task] : 0;
-    const int64_t g1 = one ? h.pan_gbegin[a.single_task + 1] : h.pan_gbegin[b->R];
     EBTC_PHASE(prof, EBTC_PHASE_PREPARE,
-               launch_pan_prepare(b->dtype, b->values != nullptr, a, x.nb, a.pan_groups + g0, (int)(g1 - g0), s));
+               launch_tile_prepare(b->dtype, b->values != nullptr, a, one ? a.single_task : 0, one ? 1 : (int)b->R, s));
     return EBTC_OK;
   }
   if (x.sp.form != EBTC_SPMV_SEGMENTED) return EBTC_OK;
@@ -1350,6 +1343,8 @@ int ebtc_tune(ebtc_batch* b, const ebtc_opts* o, void* ws, size_t ws_bytes, int3
   }
   std::map<std::string, std::array<int32_t, 3>> choice;
   constexpr int kReps = 3;
+  // Steps that share a preparation: an adaptive run stops long before its cap (12 to 22 steps on the families here).
+  const int spread = o->m > 0 ? steps : std::min(steps, 16);
   for (const std::string& key : keys) {
     {
       std::lock_guard<std::mutex> lock(g_tune_mu);
@@ -1381,8 +1376,13 @@ int ebtc_tune(ebtc_batch* b, const ebtc_opts* o, void* ws, size_t ws_bytes, int3
     cands.push_back({spmv_form(b, EBTC_SPMV_BALANCED, 0, 0, 0, mp), 8});
     {
       const SpmvPlan p = spmv_form(b, EBTC_SPMV_PANELED, 0, 0, 0, mp);
-      if (p.pmax <= kPanMaxPanels) cands.push_back({p, 9});
+      if (check_form(b, p, mp) == EBTC_OK) cands.push_back({p, 9});
+      g_err.clear();
     }
+    // The paneled form (the last candidate) takes the place of the forms whose sums it computes bit for bit. The
+    // lane-group and staged forms add a row's products in another order: a batch on which one of those is the
+    // fastest of the others stays on it, so that the paneled form's choice changes no result (staged graphs
+    // of n = 1e4 to 2.5e4 could gain a third: 77 against 56 us at 46 x n=21429, degree 25).
     int best = -1;
     double best_ms = 0.0;
     for (size_t c = 0; c < cands.size() && rc == EBTC_OK; ++c) {
@@ -1418,9 +1418,11 @@ int ebtc_tune(ebtc_batch* b, const ebtc_opts* o, void* ws, size_t ws_bytes, int3
         break;
       }
       const bool prepared = p.form == EBTC_SPMV_SEGMENTED || p.form == EBTC_SPMV_BALANCED || p.form == EBTC_SPMV_PANELED;
-      const double t = t_spmv / kReps + (prepared ? t_prep / steps : 0.0);
+      const double t = t_spmv / kReps + (prepared ? t_prep / spread : 0.0);
       ms[cands[c].slot] = (ms[cands[c].slot] < 0 ? 0.0 : ms[cands[c].slot]) + t;
-      if (best < 0 || t < best_ms) {
+      const bool stays = p.form == EBTC_SPMV_PANELED && best >= 0 &&
+                         (cands[best].p.form == EBTC_SPMV_LANE_GROUPS || cands[best].p.form == EBTC_SPMV_LDS_STAGED);
+      if (best < 0 || (t < best_ms && !stays)) {
         best = (int)c;
         best_ms = t;
       }

@@ -116,10 +116,8 @@ struct StepClose {
 
 // Closes Lanczos step j from its norm partials: beta_j = ||v~_{j+1}|| and the breakdown test
 // beta_j <= 64 eps scal[j], scal[j] = max(|alpha_0..j|, beta_0..j-1) (recorded by the update kernel
-// that finished alpha_j). Reads only values written by earlier kernels.
-__device__ inline StepClose close_step(const RState* st, const double* norm_part, int nblk, int j, double eps,
-                                       double* lds) {
-  const double ss = canonical_sum(norm_part, nblk, 1, lds);
+// that finished alpha_j). Reads only values written by earlier kernels. ss: their canonical sum.
+__device__ inline StepClose close_sum(const RState* st, double ss, int j, double eps) {
   StepClose c;
   c.beta = sqrt(ss);
   const double scale = st->scal[j];
@@ -127,6 +125,10 @@ __device__ inline StepClose close_step(const RState* st, const double* norm_part
   if (!isfinite(c.beta) || !isfinite(scale)) c.flags = EBTC_FLAG_NONFINITE;
   else if (!(c.beta > 64.0 * eps * scale)) c.flags = EBTC_FLAG_BREAKDOWN;
   return c;
+}
+__device__ inline StepClose close_step(const RState* st, const double* norm_part, int nblk, int j, double eps,
+                                       double* lds) {
+  return close_sum(st, canonical_sum(norm_part, nblk, 1, lds), j, eps);
 }
 
 }  // namespace ebtc

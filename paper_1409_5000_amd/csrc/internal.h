@@ -74,21 +74,48 @@ static_assert(sizeof(BalPart) == 16, "BalPart layout");
 // of row walks per workgroup).
 constexpr int kBalEntriesMin = 4096, kBalEntriesMax = 16384, kBalTargetShares = 8192;
 
-// One work item of the panel form's products pass: panel `panel` of row units [b0, b1) of
-// realization `task` (unit indices local to the realization). The once-per-call scan takes the same
-// struct for a group of units (panel unused).
-struct PanItem {
-  int32_t task;
-  int32_t panel;
-  int32_t b0;
-  int32_t b1;
+// Paneled form (k_tile.hip): one share of a realization's rows, with all that the first loads of a product
+// need, in launch order; a cut of them; and a batch of long rows (`count` of hub_row from `first` on).
+struct TileShare {
+  int32_t task;     // -1: the workgroup of this place has no share
+  int32_t q;        // share of the realization
+  int32_t r_begin;  // first row
+  int32_t rows;
+  int32_t n;        // order of the realization
+  int32_t nblk;     // Task::nblk of the realization
+  int32_t flag;     // kTileFlag*
+  int32_t pad;
+  int64_t vec_off, w_off, rowptr_off, part_off;  // Task's, w_off moved to the share's first row
 };
-static_assert(sizeof(PanItem) == 16, "PanItem layout");
-// Panel form: the row-sum pass's LDS for one unit's products (at most 128 KB), the largest unit
-// (rows), and the largest number of panels per realization (the sort's count table).
-constexpr int kPanCapBytes = 128 * 1024;
-constexpr int kPanMaxUnit = 256;
-constexpr int kPanMaxPanels = 1024;
+struct TileCut {
+  int32_t r_begin, r_end;
+};
+struct HubBatch {
+  int32_t task, first, count, entries;
+};
+static_assert(sizeof(TileShare) == 64 && sizeof(HubBatch) == 16, "paneled form layouts");
+constexpr int kTileBandsHost = 12;    // row bands of a share, one wave of the product each
+constexpr int kTileMaxRows = 12160;   // rows of a share: their FP64 sums beside two 32 KB slices in 160 KB
+constexpr int kTileMinRows = 512;
+constexpr int kTileMaxPanels = 1536;  // panels of the largest n accepted: 1024 x 12288 / 8192
+constexpr int64_t kTileMaxSlots = (int64_t)1 << 27;
+constexpr int kTileFlagHubs = 1, kTileFlagStream = 2;  // rows listed apart; CSR-stream arithmetic
+constexpr int kTileUnits = 256;       // compute units: shares run one to a unit
+// Entries at which a share ends early: a quarter above the mean share's, so that the head of a
+// preferential-attachment graph does not set a launch's time, while the shares of other graphs end by rows.
+__host__ __device__ inline int64_t tile_entries(int rows, int64_t n, int64_t z) {
+  const int64_t e = 5 * (int64_t)rows * z / (4 * (n > 0 ? n : 1));
+  return e > 8192 ? e : 8192;
+}
+// Fewest rows per share that k_tile_pack may choose where the host chose `rows` for so many rounds.
+__host__ __device__ inline int tile_min_rows(int rows, int rounds) {
+  return (int)((int64_t)rows * rounds / (rounds + 1)) + 1;
+}
+// Shares a realization can be cut into: every share ends by rows or holds, with the next share's first row,
+// more than tile_entries entries, and a row is counted twice at most.
+inline int64_t tile_slots(int rows, int64_t n, int64_t z) {
+  return (n + rows - 1) / rows + 2 * z / tile_entries(rows, n, z) + 1;
+}
 
 struct GraphInfo {
   int64_t score_off;   // offset of the graph's block in the score output
@@ -161,23 +188,23 @@ struct LzArgs {
   const int64_t* bal_begin;  // [R + 1] first share of each realization (host-computed)
   int32_t nbal;
   int32_t bal_entries;     // entries per share
-  // panel form (pan_cols > 0): each group of row units' entries put in (panel, unit) order once per
-  // call; each step a products pass (one vector slice in LDS serves a group's entries of a panel) and a
-  // row-sum pass per unit
+  // paneled form (pan_cols > 0), k_tile.hip
   int32_t pan_cols;        // columns per panel
-  int32_t pan_pmax;        // most panels of a realization in the launch (the stride of pan_run)
-  int32_t pan_unit;        // rows per unit (64, 128 or 256)
-  int32_t pan_lds;         // entries of a unit the row-sum pass holds in LDS (more: stream arithmetic)
-  int32_t* pan_flag;       // [units] 1 = sorted, 0 = the unit uses the CSR-stream arithmetic
-  int2* pan_run;           // [units][pan_pmax] {first entry, count} of the unit's run of panel p, entries
-                           // counted from the realization's first
-  uint16_t* pan_col;       // [entries] column - p * pan_cols
-  uint16_t* pan_perm;      // [entries] the entry's position in its unit's CSR range
-  void* pan_val;           // [entries] values in the same order (nullptr for pattern-only graphs)
-  void* pan_prod;          // [entries] the step's products, same order
-  const PanItem* pan_items;  // products-pass work items
-  const PanItem* pan_groups;  // [groups] unit groups of the once-per-call scan (panel unused)
-  int32_t pan_nitems;
+  int32_t pan_pmax;        // most panels of a realization in the launch (the stride of tile_end)
+  int32_t tile_rows;       // rows per share at most
+  int32_t ntile;           // share slots of the launch's realizations (its grid)
+  const int64_t* tile_begin;  // [R + 1] first share slot of each realization (host-computed)
+  TileCut* tile_cut;       // [slots] shares as cut, realization by realization
+  int32_t* tile_ncut;      // [R + 1] shares of each realization, then the first of them in the launch
+  TileShare* tile_share;   // [places] the launch's shares in launch order (places = slots rounded up to 8)
+  int64_t* tile_base;      // [places][kTileBands] each band's first entry in the form's arenas
+  uint32_t* tile_end;      // [places][kTileBands][pan_pmax] the band's entries up to the end of each panel
+  uint32_t* tile_ent;      // [entries] words (column, row, rank), band by band, panel by panel
+  void* tile_val;          // [entries] values in the same order (nullptr for pattern-only graphs)
+  int32_t* tile_count;     // [4] shares of the launch, long rows, batches of them, rows per share of the cut
+  int32_t tile_short;      // 1: short runs of a band's entries per panel (chunks of fewer entries)
+  int32_t* hub_row;        // long rows
+  HubBatch* hub_batch;
   // memory-bounded form (window > 0): Gram-Schmidt against the last `window` basis vectors only, the
   // raw basis kept in a ring of window + 1 slots (vector i in slot i % (window + 1))
   int32_t window;
@@ -186,8 +213,8 @@ struct LzArgs {
   // start kernel, counted by the check); every kernel of step j + 1 returns at once when it is 0
   int32_t* live;
   int32_t unit_start;      // 1: v_0 is the raw all-ones vector, so step 0's product is A's row sums
-  int32_t first_in_prepare;  // 1: the column-segmented sort also writes step 0's product (weighted
-                             // graphs), so the step sequence launches none for it
+  int32_t first_in_prepare;  // 1: the column-segmented or paneled sort also writes step 0's product
+                             // (weighted graphs), so the step sequence launches none for it
 };
 
 // Slot of basis vector i in a realization's V block.
@@ -250,15 +277,13 @@ hipError_t prepare_seg_kernels();
 hipError_t launch_seg_prepare(int dtype, bool has_val, const LzArgs& a, int64_t nblocks, int smax, hipStream_t s);
 // Row bounds of the entry-balanced form's shares of realizations [t0, t0 + count).
 hipError_t launch_bal_rows(const LzArgs& a, int t0, int count, hipStream_t s);
-// Panel form: largest panel (columns) for the products pass's LDS slice, largest LDS budget of the
-// row-sum pass (entries), and the once-per-call sort (count, scan over `groups`, place).
-int pan_max_cols(int dtype);
-int pan_max_lds(int dtype);
-// Entries of the CSR-stream arithmetic's LDS buffer (rows beyond it are summed as hub rows).
-int stream_cap(int dtype);
-hipError_t prepare_pan_kernels();
-hipError_t launch_pan_prepare(int dtype, bool has_val, const LzArgs& a, int64_t nblocks, const PanItem* groups,
-                              int ngroups, hipStream_t s);
+// ---- launchers (k_tile.hip): the paneled form
+int tile_max_cols(int dtype);           // widest panel
+int64_t tile_hub_rows(int64_t entries);  // most long rows among so many entries
+hipError_t prepare_tile_kernels();
+// The shares and the sorted entries of realizations [t0, t0 + count).
+hipError_t launch_tile_prepare(int dtype, bool has_val, const LzArgs& a, int t0, int count, hipStream_t s);
+hipError_t launch_spmv_tile(int dtype, bool has_val, int j, const LzArgs& a, hipStream_t s);
 
 // ---- launchers (k_tridiag.hip)
 // mode 0: final (closes step m_steps-1 when still open; writes y/theta/est, diag, checkpoint);

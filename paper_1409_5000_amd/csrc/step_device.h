@@ -9,6 +9,18 @@ namespace ebtc {
 namespace {
 
 // ------------------------------------------------------------------------------- phase A: SpMV
+// Records the close of step j - 1 in the realization's state (one thread).
+__device__ inline void record_close(RState* st, const StepClose& c, int j) {
+  st->beta[j - 1] = c.beta;
+  if (c.flags) {
+    st->flags |= c.flags;
+    st->done = 1;
+    st->m_used = j;
+  } else {
+    st->s[j] = 1.0 / c.beta;
+  }
+}
+
 // Opens phase A of step j: closes step j-1 from its norm partials (all workgroups of the
 // realization compute the same bits; workgroup 0 records them). Returns false when the
 // realization is finished; *sj = 1/beta_{j-1} (or s_0 at j = 0).
@@ -20,16 +32,7 @@ __device__ inline bool open_step(const LzArgs& a, const Task& tk, RState* st, in
     return true;
   }
   const StepClose c = close_step(st, npart ? npart : a.npart + tk.part_off / kPartStride, tk.nblk, j - 1, a.eps, chunks);
-  if (blk == 0 && threadIdx.x == 0) {
-    st->beta[j - 1] = c.beta;
-    if (c.flags) {
-      st->flags |= c.flags;
-      st->done = 1;
-      st->m_used = j;
-    } else {
-      st->s[j] = 1.0 / c.beta;
-    }
-  }
+  if (blk == 0 && threadIdx.x == 0) record_close(st, c, j);
   if (c.flags) return false;
   *sj = 1.0 / c.beta;
   return true;

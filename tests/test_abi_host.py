@@ -199,6 +199,24 @@ def test_plan_segmented_workspace_arithmetic():
     A.lib().ebtc_batch_destroy(h)
 
 
+@pytest.mark.parametrize("dtype,cols", [(A.EBTC_F32, 12288), (A.EBTC_F64, 6144)])
+def test_plan_paneled_limits(dtype, cols):
+    # at most 1024 panels of the columns asked for (more than the default count as the default), and the
+    # kernels' arenas: a word per entry and the value, besides the tables
+    for n, seg_len, ok in [(1024 * cols, 0, True), (1024 * cols + 1, 0, False), (1024 * cols, 10 * cols, True),
+                           (1024 * 100, 100, True), (1024 * 100 + 1, 100, False), (1, 1, True)]:
+        d, keep = make_desc(G=1, nreal=(1,), n=(n,), nnz=(1000,), dtype=dtype)
+        rc, h = create(d)
+        assert rc == 0
+        rc, ws, _ = plan(h, m=3, spmv=6, seg_len=seg_len)
+        assert (rc == 0) == ok, (n, seg_len)
+        if ok:
+            assert ws >= plan(h, m=3, spmv=1)[1] + 4 * 1000
+        else:
+            assert "1024 panels" in A.lib().ebtc_last_error().decode()
+        A.lib().ebtc_batch_destroy(h)
+
+
 def set_forms(h, forms, lanes=None, seg=None):
     f = np.array(forms, np.int32)
     l = None if lanes is None else np.array(lanes, np.int32)

@@ -1,0 +1,111 @@
+"""The paneled SpMV form's kernels at the sizes where they can go wrong, against the CSR-stream form, bit for
+bit, through whole Lanczos runs: rows on both sides of each limit of the long-row path, more panels than one
+load of the panel ends covers, bands of no, one and many rows, realizations of very different sizes in one
+launch, columns out of order (a share of the stream arithmetic), shares that end early by their entries.
+
+The form adds every row's products in entry order in FP64 as the stream form does, so the tolerance is zero.
+"""
+import numpy as np
+import pytest
+
+from fixtures import graphs as G
+
+pytestmark = pytest.mark.gpu
+
+
+def api():
+    from paper_1409_5000_amd import api as _api
+    return _api
+
+
+def scored(b, **kw):
+    import torch
+    out = b.scores(schedule=kw.pop("schedule", "batched"), **kw)
+    torch.cuda.synchronize()
+    return out.scores.cpu().numpy().tobytes(), out.log_scale.cpu().numpy().tobytes(), out.diag_numpy().tobytes()
+
+
+def csr(n, keys, rng, values):
+    rp, ci = G.csr_from_keys(np.unique(keys[(keys // n) != (keys % n)]), n)
+    return (rp, ci, 0.5 + rng.random(ci.size)) if values else (rp, ci)
+
+
+def hubs(n, rows, rng):
+    """A sparse background and rows of given lengths."""
+    parts = [G.er_keys(n, 5.0 / (n - 1), rng)]
+    for h, length in rows:
+        parts.append(G.canon(np.full(length, h), rng.choice(n, length, replace=False), n))
+    return np.concatenate(parts)
+
+
+@pytest.mark.parametrize("dtype,values", [("f32", True), ("f32", False), ("f64", True), ("f64", False)])
+def test_long_rows(gpu_lib, dtype, values):
+    # around the long-row limit (256), a chunk of products (512), the stream form's capacity (6144 FP32,
+    # 3072 FP64) and a batch of products (32768 FP32, 16384 FP64), many of them in one group of 64 rows
+    n = 50_000
+    rng = np.random.default_rng(3)
+    rows = [(5, 240), (6, 249), (7, 255), (8, 262), (70, 500), (71, 513), (72, 1030), (9000, 3071), (9001, 3100),
+            (9002, 6140), (9003, 6200), (30000, 16400), (30001, 33000), (49999, 40000)]
+    rows += [(20000 + i, 300 + 7 * i) for i in range(80)]
+    b = api().Batch.from_csr([[csr(n, hubs(n, rows, rng), rng, values)]], dtype=dtype)
+    ref = scored(b, m=8, spmv="stream")
+    assert scored(b, m=8, spmv="paneled") == ref
+    assert scored(b, m=8, spmv="paneled", seg_len=700) == ref  # 72 panels: two loads of panel ends per band
+    assert scored(b, m=8, spmv="paneled", schedule="plain") == ref
+
+
+@pytest.mark.parametrize("dtype,values", [("f32", True), ("f64", False)])
+def test_sizes_in_one_launch(gpu_lib, dtype, values):
+    # empty, single-node and tiny graphs beside one of several shares; seg_len 100: more than 64 panels
+    rng = np.random.default_rng(5)
+    graphs = []
+    for n in (1, 2, 3, 63, 64, 65, 511, 512, 513, 4097, 12160, 12161, 30011):
+        d = min(8.0, max(0, n - 1))
+        keys = G.er_keys(n, d / max(1, n - 1), rng) if n > 1 else np.empty(0, np.int64)
+        graphs.append([csr(n, keys, rng, values), csr(n, np.empty(0, np.int64), rng, values)])
+    b = api().Batch.from_csr(graphs, dtype=dtype)
+    ref = scored(b, m=6, spmv="stream")
+    for kw in (dict(), dict(seg_len=100), dict(seg_len=8191), dict(hipgraph=False), dict(schedule="plain")):
+        assert scored(b, m=6, spmv="paneled", **kw) == ref, kw
+    assert scored(b, m=6, spmv="paneled", reorth=0) == scored(b, m=6, spmv="stream", reorth=0)
+
+
+def test_columns_out_of_order(gpu_lib):
+    # two rows with swapped columns: their share takes the stream arithmetic, the other shares stay sorted
+    n = 40_000
+    rng = np.random.default_rng(7)
+    rp, ci, va = csr(n, G.er_keys(n, 12.0 / (n - 1), rng), rng, True)
+    for r in (17, 25_000):
+        k = int(rp[r])
+        assert rp[r + 1] - k >= 2
+        ci[[k, k + 1]], va[[k, k + 1]] = ci[[k + 1, k]], va[[k + 1, k]]
+    b = api().Batch.from_csr([[(rp, ci, va)]], dtype="f32")
+    ref = scored(b, m=10, spmv="stream")
+    assert scored(b, m=10, spmv="paneled") == ref
+    assert scored(b, m=10, spmv="paneled", seg_len=1000) == ref
+
+
+def test_shares_that_end_early(gpu_lib):
+    # preferential attachment with 40 realizations: heads cut by entries, and the rows per share chosen anew
+    n = 30_000
+    rng = np.random.default_rng(9)
+    reals = [csr(n, G.ba_keys(n, 8, rng), rng, False) for _ in range(40)]
+    b = api().Batch.from_csr([reals], dtype="f32")
+    ref = scored(b, m=0, tol=1e-6, m_max=40, spmv="stream")
+    assert scored(b, m=0, tol=1e-6, m_max=40, spmv="paneled") == ref
+    assert scored(b, m=0, tol=1e-6, m_max=40, spmv="paneled") == ref  # a replay
+
+
+def test_adjoint_on_tiles(gpu_lib):
+    # the adjoint's solve starts at the cotangent: step 0 runs the product kernel
+    import torch
+    n = 26_001
+    rng = np.random.default_rng(11)
+    rows = [(3, 700), (25_999, 4000)]
+    b = api().Batch.from_csr([[csr(n, hubs(n, rows, rng), rng, True) for _ in range(2)]], dtype="f32")
+    g = torch.as_tensor(rng.normal(size=n)).to("cuda")
+    grads = []
+    for form in ("stream", "paneled"):
+        out = b.scores(m=12, schedule="batched", spmv=form)
+        grads.append(b.scores_backward(out.log_scale, g, m=12, spmv=form).cpu().numpy().tobytes())
+    assert grads[0] == grads[1]
