@@ -1,7 +1,8 @@
 // Realization generator for gfx950: background graphs drawn on the device (G(n, p), Watts-Strogatz,
 // Barabasi-Albert), the target pattern embedded, written as the batch's symmetric CSR.
 //
-// One ebtc_generate_count call (count realizations of one spec):
+// One ebtc_generate_count call (count realizations of one spec), where the graphs are too large or too dense for
+// the assembly from bins of rows (below, "binned assembly"):
 //   1. candidates: a thread per row (G(n, p): geometric skips, run twice -- count, scan, write) or per
 //      lattice / attachment edge (WS, BA) writes the 64-bit key (r, min, max) of every drawn edge;
 //      an edge with both ends among the target nodes becomes the invalid key; the pattern's edges
@@ -160,8 +161,19 @@ __global__ __launch_bounds__(kGenBlock) void k_er_tail(const int64_t* hdr, uint6
   if (t < cap && t >= hdr[kHdrCandidates]) keys[t] = kInvalidKey;
 }
 
+// An edge to its slot: the 64-bit key, or the pair (binned assembly: slot of a realization's region of `reg`
+// slots; (-1, -1) for an edge inside the target set).
+__device__ inline void put_edge(const GenArgs& a, uint64_t* keys, int64_t, int rl, int64_t e, int x, int y) {
+  keys[(int64_t)rl * a.per + e] = edge_key(a, rl, x, y);
+}
+__device__ inline void put_edge(const GenArgs& a, int2* pairs, int64_t reg, int rl, int64_t e, int x, int y) {
+  const bool in = a.inside && a.inside[x] && a.inside[y];
+  pairs[(int64_t)rl * reg + e] = in ? make_int2(-1, -1) : make_int2(x, y);
+}
+
 // Watts-Strogatz: lattice edge e of realization rl, rewired or kept.
-__global__ __launch_bounds__(kGenBlock) void k_ws_edges(GenArgs a, uint64_t* keys) {
+template <typename E>
+__global__ __launch_bounds__(kGenBlock) void k_ws_edges(GenArgs a, E* out, int64_t reg) {
   const int64_t t = gtid();
   if (t >= (int64_t)a.count * a.per) return;
   const int rl = (int)(t / a.per);
@@ -172,7 +184,7 @@ __global__ __launch_bounds__(kGenBlock) void k_ws_edges(GenArgs a, uint64_t* key
   uint32_t w[4];
   philox4x32_10((uint32_t)e, 0u, (uint32_t)(a.first + rl), kTagWS, a.k0, a.k1, w);
   const int nv = (int)((i + 1 + (int64_t)(((uint64_t)w[1] * (uint64_t)(n - 1)) >> 32)) % n);
-  keys[t] = edge_key(a, rl, i, (uint64_t)w[0] < a.thr ? nv : far);
+  put_edge(a, out, reg, rl, e, i, (uint64_t)w[0] < a.thr ? nv : far);
 }
 
 // Barabasi-Albert: the node that brings edge e (seed star: leaf e + 1).
@@ -192,7 +204,8 @@ __device__ inline int64_t ba_slot(const GenArgs& a, uint32_t ridx, int64_t e) {
 // Barabasi-Albert edge e of realization rl: its node and the endpoint found by following odd slots
 // (the attached end of an earlier edge) back to an even slot (a new node) or the seed's centre. Each
 // hop moves to a strictly earlier edge, so the walk ends.
-__global__ __launch_bounds__(kGenBlock) void k_ba_edges(GenArgs a, uint64_t* keys) {
+template <typename E>
+__global__ __launch_bounds__(kGenBlock) void k_ba_edges(GenArgs a, E* out, int64_t reg) {
   const int64_t t = gtid();
   if (t >= (int64_t)a.count * a.per) return;
   const int rl = (int)(t / a.per);
@@ -215,7 +228,7 @@ __global__ __launch_bounds__(kGenBlock) void k_ba_edges(GenArgs a, uint64_t* key
       s = ba_slot(a, ridx, f);
     }
   }
-  keys[t] = edge_key(a, rl, ba_new_node(m, e), end);
+  put_edge(a, out, reg, rl, e, ba_new_node(m, e), end);
 }
 
 // Target membership flags.
@@ -465,6 +478,478 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(const uint64_t* 
   }
 }
 
+// ------------------------------------------------------------------------------- binned assembly
+// The sorts above move every key through memory about twenty times (64 x n=1e5, degree 20: 14 ms of radix
+// passes, and 5 ms of degree counts by 128M global atomics). Where a few hundred rows' entries fit one
+// workgroup's LDS, the CSR is assembled from bins of rows instead:
+//   draw      the edges as pairs, each realization in a region of its own, in any order (G(n, p): one pass;
+//             a workgroup collects its rows' edges in LDS and appends them to the region);
+//   count     both ends' bins of every pair, in LDS per chunk of pairs, then one atomic per chunk and bin;
+//   scatter   chunk by chunk: (row in the bin, column) of both directions, grouped by bin in LDS and written
+//             to the bins' ranges in runs;
+//   sort      one workgroup per bin: grouped by row and ranked within the row in LDS, repeats dropped, the
+//             columns and the rows' degrees written; a bin beyond the LDS is sorted in memory by its workgroup;
+//   fill      bin by bin, contiguous copies.
+// Orders inside regions, bins and rows vary from run to run up to the sort, which removes the difference.
+// Bins of G(n, p) and Watts-Strogatz graphs hold equal rows; those of Barabasi-Albert graphs equal expected
+// entries: a node u n holds k edges of its own and k / sqrt(u) / 2 of later ones, so the first u n rows hold
+// the share (u + sqrt(u)) / 2.
+// 64 x n=1e5, degree 20: 18.4 to 2.42 ms; 8 x n=300007 Barabasi-Albert, k = 8: 6.74 to 1.34 ms (whole calls).
+constexpr int kBinCap = 8192;      // entries of a bin sorted in LDS
+constexpr int kBinFill = 6144;     // expected entries of a bin at most
+constexpr int kBinRows = 512;      // rows of a bin at most
+constexpr int kBinMax = 8192;      // bins of a realization at most
+constexpr int kBinColBits = 21;    // columns: n <= 2^21
+constexpr int kBinThreads = 1024;  // count and scatter
+constexpr int kBinSort = 512;      // sort
+constexpr int kBinPairs = 4;       // pairs per thread of the scatter, half of the count's
+constexpr int kErCap = 8192;       // edges a workgroup of rows collects in LDS
+
+struct BinArgs {
+  const int32_t* first;  // [nb + 1] first row of each bin
+  int32_t nb, shift;     // shift >= 0: 2^shift rows per bin; -1: by expected entries
+  int64_t reg;           // pair slots of a realization: per background edges, then pe pattern edges
+  int2* pairs;           // [count][reg]
+  int32_t* drawn;        // [count] background pairs (G(n, p); may exceed per: overflow)
+  uint32_t* bcount;      // [count][nb] entries of each bin, then the first entry of each in its realization
+  uint32_t* bcursor;     // [count][nb] next free entry
+  uint32_t* ent;         // [count][2 reg] words (row in the bin << 21 | column)
+  uint32_t* cols;        // [count][2 reg] sorted columns, bin by bin
+};
+
+__device__ inline int bin_of(const BinArgs& b, int n, int row) {
+  if (b.shift >= 0) return row >> b.shift;
+  const float u = ((float)row + 0.5f) / (float)n;
+  int k = min(b.nb - 1, max(0, (int)(0.5f * (u + sqrtf(u)) * (float)b.nb)));
+  while (row < b.first[k]) --k;
+  while (row >= b.first[k + 1]) ++k;
+  return k;
+}
+
+__device__ inline int row_in_bin(const BinArgs& b, int k, int row) {
+  return b.shift >= 0 ? row & ((1 << b.shift) - 1) : row - b.first[k];
+}
+
+// First rows of the bins; the call's counters at their starts (`drawn` background pairs per realization).
+__global__ __launch_bounds__(kGenBlock) void k_bin_init(BinArgs b, int n, int64_t cells, int count, int32_t drawn,
+                                                        int32_t* first, int64_t* hdr) {
+  const int64_t t = gtid();
+  if (t < cells) b.bcount[t] = 0;
+  if (t < count) b.drawn[t] = drawn;
+  if (t < kHdrWords) hdr[t] = 0;
+  if (t <= b.nb) {
+    int64_t r;
+    if (b.shift >= 0) {
+      r = t << b.shift;
+    } else {  // u + sqrt(u) = 2 t / nb
+      const double q = 0.5 * (sqrt(1.0 + 8.0 * (double)t / (double)b.nb) - 1.0);
+      r = (int64_t)floor(q * q * (double)n);
+    }
+    first[t] = t == b.nb ? n : (int32_t)min(r, (int64_t)n);
+  }
+}
+
+// Bounds of a chunk's pairs that hold something: [0, drawn) and [per, reg).
+__device__ inline bool pair_valid(const GenArgs& a, int64_t drawn, int64_t k) {
+  return k < drawn || k >= a.per;
+}
+
+// G(n, p): a thread per row as in k_er_rows, one pass. `wgs` workgroups per realization. Bound by Philox and the
+// logarithms: 0.43 ms for 64M edges, of which their 0.5 GB would take 0.1.
+__global__ __launch_bounds__(kGenBlock) void k_er_append(GenArgs a, BinArgs b, int wgs) {
+  __shared__ uint32_t buf[kErCap];  // row in the workgroup << 21 | column
+  __shared__ int cnt, base;
+  const int rl = blockIdx.x / wgs, i0 = (blockIdx.x - rl * wgs) * kGenBlock, i = i0 + threadIdx.x, n = a.n;
+  if (threadIdx.x == 0) cnt = 0;
+  __syncthreads();
+  int2* out = b.pairs + (int64_t)rl * b.reg;
+  auto emit = [&](int j) {
+    if (a.inside && a.inside[i] && a.inside[j]) return;
+    const int at = atomicAdd(&cnt, 1);
+    if (at < kErCap) {
+      buf[at] = (uint32_t)threadIdx.x << kBinColBits | (uint32_t)j;
+    } else {  // the workgroup's rows hold more than its buffer
+      const int g = atomicAdd(&b.drawn[rl], 1);
+      if (g < a.per) out[g] = make_int2(i, j);
+    }
+  };
+  if (i < n - 1) {
+    if (a.p >= 1.0) {
+      for (int j = i + 1; j < n; ++j) emit(j);
+    } else if (a.p > 0.0 && 1.0 - a.p != 1.0) {
+      const double q = exact_log(1.0 - a.p);
+      const uint32_t ridx = (uint32_t)(a.first + rl);
+      int64_t j = i;
+      bool more = true;
+      for (uint32_t call = 0; more; ++call) {
+        uint32_t w[4];
+        philox4x32_10((uint32_t)i, call, ridx, kTagER, a.k0, a.k1, w);
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+          if (more) {
+            const double u = ((double)w[h] + 0.5) * 0x1p-32;
+            const double g = floor(exact_log(u) / q);
+            if (g < (double)(n - 1 - j)) {
+              j += 1 + (int64_t)g;
+              emit((int)j);
+            } else {
+              more = false;
+            }
+          }
+        }
+      }
+    }
+  }
+  __syncthreads();
+  const int m = min(cnt, kErCap);
+  if (threadIdx.x == 0) base = m > 0 ? atomicAdd(&b.drawn[rl], m) : 0;
+  __syncthreads();
+  for (int k = threadIdx.x; k < m; k += kGenBlock)
+    if (base + k < a.per)
+      out[base + k] = make_int2(i0 + (int)(buf[k] >> kBinColBits), (int)(buf[k] & ((1u << kBinColBits) - 1u)));
+}
+
+// The pattern's edges at the end of every realization's region.
+__global__ __launch_bounds__(kGenBlock) void k_bin_pattern(GenArgs a, BinArgs b, const int32_t* targets,
+                                                           const int32_t* pattern) {
+  const int64_t t = gtid();
+  if (t >= (int64_t)a.count * a.pe) return;
+  const int rl = (int)(t / a.pe), q = (int)(t - (int64_t)rl * a.pe);
+  b.pairs[(int64_t)rl * b.reg + a.per + q] = make_int2(targets[pattern[2 * q]], targets[pattern[2 * q + 1]]);
+}
+
+// A thread's pairs of a chunk of PP kBinThreads; (-1, -1) where there is none.
+template <int PP>
+__device__ inline void load_pairs(const GenArgs& a, const BinArgs& b, int rl, int64_t k0, int64_t drawn, int2 (&e)[PP]) {
+  const int2* in = b.pairs + (int64_t)rl * b.reg;
+#pragma unroll
+  for (int u = 0; u < PP; ++u) {
+    const int64_t k = k0 + u * kBinThreads + threadIdx.x;
+    e[u] = k < b.reg && pair_valid(a, drawn, k) ? in[k] : make_int2(-1, -1);
+  }
+}
+
+// Entries of each bin: one workgroup per chunk of pairs of a realization (`chunks` of them).
+__global__ __launch_bounds__(kBinThreads) void k_bin_count(GenArgs a, BinArgs b, int chunks, int64_t* hdr) {
+  constexpr int PP = 2 * kBinPairs;
+  extern __shared__ __align__(16) uint32_t bin_lds[];
+  const int rl = blockIdx.x / chunks, tid = threadIdx.x;
+  const int64_t drawn = b.drawn[rl];
+  if (drawn > a.per && tid == 0) hdr[kHdrOverflow] = 1;
+  int2 e[PP];
+  load_pairs(a, b, rl, (int64_t)(blockIdx.x - rl * chunks) * (PP * kBinThreads), drawn, e);
+  for (int i = tid; i < b.nb; i += kBinThreads) bin_lds[i] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < PP; ++u)
+    if (e[u].x >= 0) {
+      atomicAdd(&bin_lds[bin_of(b, a.n, e[u].x)], 1u);
+      atomicAdd(&bin_lds[bin_of(b, a.n, e[u].y)], 1u);
+    }
+  __syncthreads();
+  for (int i = tid; i < b.nb; i += kBinThreads)
+    if (bin_lds[i]) atomicAdd(&b.bcount[(int64_t)rl * b.nb + i], bin_lds[i]);
+}
+
+// Exclusive prefix sum of x[0, len) in place by the workgroup (1024 threads); copy also receives it. Returns the
+// sum.
+__device__ inline int bin_scan(uint32_t* x, uint32_t* copy, int len, int64_t* wtot) {
+  const int per = (len + kBinThreads - 1) / kBinThreads, i0 = min((int)threadIdx.x * per, len), i1 = min(i0 + per, len);
+  int64_t sum = 0, total;
+  for (int i = i0; i < i1; ++i) sum += x[i];
+  int64_t run = block_excl_scan64<kBinThreads>(sum, wtot, &total);
+  for (int i = i0; i < i1; ++i) {
+    const uint32_t v = x[i];
+    x[i] = (uint32_t)run;
+    if (copy) copy[i] = (uint32_t)run;
+    run += v;
+  }
+  return (int)total;
+}
+__global__ __launch_bounds__(kBinThreads) void k_bin_starts(BinArgs b) {
+  __shared__ int64_t wtot[kBinThreads / 64];
+  bin_scan(b.bcount + (int64_t)blockIdx.x * b.nb, b.bcursor + (int64_t)blockIdx.x * b.nb, b.nb, wtot);
+}
+
+// Both directions of a chunk's pairs to their bins: the counts per bin give every word its rank, their scan its
+// place in LDS, and runs of the bins' words go out. Four pairs per thread, so that two workgroups fit a compute unit
+// (eight: longer runs, but 0.52 ms instead of 0.45 for 64M pairs). LDS: the counts, then first places; where each bin's run
+// goes; the words and their bins in bin order.
+__global__ __launch_bounds__(kBinThreads) void k_bin_scatter(GenArgs a, BinArgs b, int chunks) {
+  constexpr int PP = kBinPairs, chunk = PP * kBinThreads;
+  extern __shared__ __align__(16) uint32_t bin_lds[];
+  __shared__ int64_t wtot[kBinThreads / 64];
+  uint32_t *start = bin_lds, *dest = start + b.nb, *word = dest + b.nb;
+  uint16_t* bin = (uint16_t*)(word + 2 * chunk);
+  const int rl = blockIdx.x / chunks, tid = threadIdx.x;
+  int2 e[PP];
+  load_pairs(a, b, rl, (int64_t)(blockIdx.x - rl * chunks) * chunk, b.drawn[rl], e);
+  for (int i = tid; i < b.nb; i += kBinThreads) start[i] = 0;
+  __syncthreads();
+  uint32_t rx[PP], ry[PP];
+#pragma unroll
+  for (int u = 0; u < PP; ++u)
+    if (e[u].x >= 0) {
+      rx[u] = atomicAdd(&start[bin_of(b, a.n, e[u].x)], 1u);
+      ry[u] = atomicAdd(&start[bin_of(b, a.n, e[u].y)], 1u);
+    }
+  __syncthreads();
+  for (int i = tid; i < b.nb; i += kBinThreads)
+    dest[i] = start[i] ? atomicAdd(&b.bcursor[(int64_t)rl * b.nb + i], start[i]) : 0u;
+  __syncthreads();
+  const int total = bin_scan(start, nullptr, b.nb, wtot);
+  __syncthreads();
+  auto place = [&](int row, int col, uint32_t rank) {
+    const int k = bin_of(b, a.n, row);
+    const uint32_t at = start[k] + rank;
+    word[at] = (uint32_t)row_in_bin(b, k, row) << kBinColBits | (uint32_t)col;
+    bin[at] = (uint16_t)k;
+  };
+#pragma unroll
+  for (int u = 0; u < PP; ++u)
+    if (e[u].x >= 0) {
+      place(e[u].x, e[u].y, rx[u]);
+      place(e[u].y, e[u].x, ry[u]);
+    }
+  __syncthreads();
+  uint32_t* out = b.ent + 2 * (int64_t)rl * b.reg;
+  for (int i = tid; i < total; i += kBinThreads) out[dest[bin[i]] + ((uint32_t)i - start[bin[i]])] = word[i];
+}
+
+// Sorts len words in memory by all their bits, by this workgroup alone (LSD radix, 8-bit digits; tmp: len words;
+// lds: kRadix (1 + wavefronts) words). The result is in x.
+__device__ inline void bin_radix(uint32_t* x, uint32_t* tmp, int len, uint32_t* lds) {
+  constexpr int NW = kBinSort / 64;
+  uint32_t* base = lds;
+  uint32_t(*wc)[kRadix] = (uint32_t(*)[kRadix])(lds + kRadix);  // counts per wavefront and digit
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const uint64_t below = (1ull << lane) - 1ull;
+  for (int shift = 0; shift < 32; shift += 8) {
+    const uint32_t* src = (shift & 8) ? tmp : x;
+    uint32_t* dst = (shift & 8) ? x : tmp;
+    for (int d = tid; d < kRadix; d += kBinSort) base[d] = 0;
+    __syncthreads();
+    for (int i = tid; i < len; i += kBinSort) atomicAdd(&base[(src[i] >> shift) & (kRadix - 1)], 1u);
+    __syncthreads();
+    if (tid < 64) {  // four digits per lane
+      uint32_t c[4], sum = 0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        c[q] = base[4 * lane + q];
+        sum += c[q];
+      }
+      uint32_t run = sum;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t t = __shfl_up(run, o, 64);
+        if (lane >= o) run += t;
+      }
+      run -= sum;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        base[4 * lane + q] = run;
+        run += c[q];
+      }
+    }
+    __syncthreads();
+    for (int i0 = 0; i0 < len; i0 += kBinSort) {
+      const int i = i0 + tid;
+      const bool valid = i < len;
+      const uint32_t key = valid ? src[i] : 0u;
+      const int d = (int)((key >> shift) & (kRadix - 1));
+      uint64_t peers = __ballot(valid);
+#pragma unroll
+      for (int bit = 0; bit < 8; ++bit) {
+        const bool on = (d >> bit) & 1;
+        const uint64_t m = __ballot(on);
+        peers &= on ? m : ~m;
+      }
+      const int rank = __popcll(peers & below);
+      for (int q = lane; q < kRadix; q += 64) wc[w][q] = 0;
+      __syncthreads();
+      if (valid && rank == 0) wc[w][d] = (uint32_t)__popcll(peers);
+      __syncthreads();
+      uint32_t tot = 0;
+      if (tid < kRadix) {
+        for (int v = 0; v < NW; ++v) {
+          const uint32_t c = wc[v][tid];
+          wc[v][tid] = (uint32_t)tot;
+          tot += c;
+        }
+      }
+      __syncthreads();
+      if (valid) dst[base[d] + wc[w][d] + rank] = key;
+      __syncthreads();
+      if (tid < kRadix) base[tid] += tot;
+      __syncthreads();
+    }
+  }
+}
+
+// One workgroup per bin: its entries sorted by row, then column, repeats dropped; the columns to the bin's
+// range of `cols`, the rows' degrees to deg. Entries of up to kRankRow per row are ranked (each counts the smaller
+// ones of its row) and placed in the one LDS array, so that four workgroups fit a compute unit (two arrays and
+// a radix sort in them, two workgroups: 0.97 ms for the 128M entries of 64 x n=1e5, degree 20, instead of 0.79;
+// their 1 GB takes 0.23 at the fill's rate). LDS round trips and barriers bound it. A bin with a longer row, or beyond the LDS, is sorted in memory.
+constexpr int kRankRow = 512;
+__global__ __launch_bounds__(kBinSort, 8) void k_bin_sort(GenArgs a, BinArgs b, int32_t* deg) {
+  constexpr int NT = kBinSort, PER = kBinCap / NT, NW = NT / 64;
+  __shared__ uint32_t x[kBinCap + 4];
+  __shared__ int rstart[kBinRows + 1], rnext[kBinRows];
+  __shared__ int wsum[PER * NW + 1], longest;
+  constexpr uint32_t kCol = (1u << kBinColBits) - 1u, kHead = 1u << 31;
+  // every realization's first bins first: those of Barabasi-Albert hubs take longest
+  const int k = blockIdx.x / a.count, rl = blockIdx.x - k * a.count, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const uint32_t* starts = b.bcount + (int64_t)rl * b.nb;
+  const uint32_t s0 = starts[k];
+  const int cnt = (int)(b.bcursor[(int64_t)rl * b.nb + k] - s0);
+  const int row0 = b.first[k], rows = b.first[k + 1] - row0;
+  uint32_t* in = b.ent + 2 * (int64_t)rl * b.reg + s0;
+  uint32_t* out = b.cols + 2 * (int64_t)rl * b.reg + s0;
+  int32_t* dg = deg + (int64_t)rl * a.n + row0;
+  for (int r = tid; r <= rows; r += NT) rstart[r] = 0;
+  if (tid == 0) longest = cnt > kBinCap;
+  __syncthreads();
+  const uint64_t below = (1ull << lane) - 1ull;
+  uint32_t e[PER];
+  if (cnt <= kBinCap) {
+#pragma unroll
+    for (int u = 0; u < PER; ++u) e[u] = u * NT + tid < cnt ? in[u * NT + tid] : 0u;
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+      if (u * NT + tid < cnt) atomicAdd(&rstart[e[u] >> kBinColBits], 1);
+    __syncthreads();
+    static_assert(kBinRows <= NT, "a row per thread");
+    const int c = tid < rows ? rstart[tid] : 0;
+    int inc = c;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(inc, o, 64);
+      if (lane >= o) inc += t;
+    }
+    if (lane == 63) wsum[wv] = inc;
+    if (c > kRankRow) longest = 1;
+    __syncthreads();
+    int run = inc - c;
+    for (int v = 0; v < wv; ++v) run += wsum[v];
+    if (tid < rows) rstart[tid] = rnext[tid] = run;
+    if (tid == 0) rstart[rows] = cnt;
+    __syncthreads();
+  }
+  if (longest) {
+    bin_radix(in, out, cnt, x);
+    for (int r = tid; r < rows; r += NT) rstart[r] = 0;
+    __syncthreads();
+    int carry = 0;
+    for (int i0 = 0; i0 < cnt; i0 += NT) {  // first occurrences, in order
+      const int i = i0 + tid;
+      const uint32_t key = i < cnt ? in[i] : 0u;
+      const bool keep = i < cnt && (i == 0 || in[i - 1] != key);
+      const uint64_t m = __ballot(keep);
+      if (lane == 0) wsum[wv] = __popcll(m);
+      __syncthreads();
+      int before = 0, all = 0;
+      for (int v = 0; v < NW; ++v) {
+        before += v < wv ? wsum[v] : 0;
+        all += wsum[v];
+      }
+      if (keep) {
+        out[carry + before + __popcll(m & below)] = key & kCol;
+        atomicAdd(&rstart[key >> kBinColBits], 1);
+      }
+      carry += all;
+      __syncthreads();
+    }
+    for (int r = tid; r < rows; r += NT) dg[r] = rstart[r];
+    return;
+  }
+#pragma unroll
+  for (int u = 0; u < PER; ++u)
+    if (u * NT + tid < cnt) x[atomicAdd(&rnext[e[u] >> kBinColBits], 1)] = e[u];
+  if (tid < 4) x[cnt + tid] = ~0u;
+  __syncthreads();
+  // Neighbouring lanes share rows here, so that their reads coincide (lanes in the order of `ent`: 1.5 times the
+  // kernel's time). Four at a time: what follows the row is larger.
+  uint32_t col[PER], rank[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int i = u * NT + tid;
+    uint32_t w = 0, p = 0;
+    asm volatile("" ::: "memory");  // one entry's row at a time: hoisted, the rows' bounds cost 100 registers
+    if (i < cnt) {
+      w = x[i];
+      const int r = (int)(w >> kBinColBits), q0 = rstart[r], q1 = rstart[r + 1];
+      p = (uint32_t)q0;
+      for (int q = q0; q < q1; q += 4) {
+        const uint32_t o0 = x[q], o1 = x[q + 1], o2 = x[q + 2], o3 = x[q + 3];
+        p += (o0 < w + (q < i)) + (o1 < w + (q + 1 < i)) + (o2 < w + (q + 2 < i)) + (o3 < w + (q + 3 < i));
+      }
+    }
+    col[u] = w & kCol;
+    rank[u] = p;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < PER; ++u)
+    if (u * NT + tid < cnt) x[rank[u]] = col[u];
+  __syncthreads();
+  for (int r = tid; r < rows; r += NT)
+    if (rstart[r + 1] > rstart[r]) x[rstart[r]] |= kHead;
+  __syncthreads();
+  // kept entries: a row's first, and those that differ from the one before; their places in order
+  uint32_t v[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int i = u * NT + tid;
+    v[u] = i < cnt ? x[i] : 0u;
+    const bool keep = i < cnt && ((v[u] & kHead) || (x[max(i - 1, 0)] & kCol) != v[u]);
+    if (keep) v[u] |= kHead;
+    const uint64_t m = __ballot(keep);
+    if (lane == 0) wsum[u * NW + wv] = __popcll(m);
+  }
+  __syncthreads();
+  if (tid < 64) {  // PER NW = 128 sums, two per lane
+    static_assert(PER * NW == 128, "two sums per lane");
+    const int x0 = wsum[2 * lane], x1 = wsum[2 * lane + 1];
+    int inc = x0 + x1;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(inc, o, 64);
+      if (lane >= o) inc += t;
+    }
+    wsum[2 * lane] = inc - x0 - x1;
+    wsum[2 * lane + 1] = inc - x1;
+    if (lane == 63) wsum[128] = inc;
+  }
+  __syncthreads();
+  const int total = wsum[PER * NW];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const uint64_t m = __ballot((v[u] & kHead) != 0);
+    const int pos = wsum[u * NW + wv] + __popcll(m & below);
+    if (v[u] & kHead) out[pos] = v[u] & kCol;
+    if (u * NT + tid < cnt) x[u * NT + tid] = (uint32_t)pos;  // kept entries before this one
+  }
+  __syncthreads();
+  for (int r = tid; r < rows; r += NT) {
+    const int q0 = rstart[r], q1 = rstart[r + 1];
+    dg[r] = q1 > q0 ? (q1 < cnt ? (int)x[q1] : total) - (int)x[q0] : 0;
+  }
+}
+
+// The bins' columns to the caller's arrays: S is the exclusive scan of the concatenated degrees.
+__global__ __launch_bounds__(kGenBlock) void k_bin_fill(GenArgs a, BinArgs b, const int64_t* S, const int32_t* deg,
+                                                        const int64_t* dest, const int32_t* ok, int32_t* col_idx) {
+  const int rl = blockIdx.x / b.nb, k = blockIdx.x - rl * b.nb;
+  if (!ok[rl]) return;
+  const int r0 = b.first[k], r1 = b.first[k + 1];
+  if (r1 <= r0) return;
+  const int64_t base = (int64_t)rl * a.n, f = S[base + r0], e = S[base + r1 - 1] + deg[base + r1 - 1];
+  const uint32_t* in = b.cols + 2 * (int64_t)rl * b.reg + b.bcount[(int64_t)rl * b.nb + k];
+  int32_t* out = col_idx + dest[rl] + (f - S[base]);
+  for (int64_t i = threadIdx.x; i < e - f; i += kGenBlock) out[i] = (int32_t)in[i];
+}
+
 // ------------------------------------------------------------------------------------ host side
 size_t align_up(size_t x) { return (x + 255) / 256 * 256; }
 unsigned grid(int64_t threads) { return (unsigned)((threads + kGenBlock - 1) / kGenBlock); }
@@ -524,6 +1009,10 @@ struct GenPlan {
   int64_t cap = 0;         // + pattern edges of every realization
   uint64_t limit = 0;      // count n^2: every valid key is below it
   int end_bit = 1;
+  // binned assembly (nb > 0): bins per realization, log2 of their rows (-1: by expected entries)
+  int nb = 0, shift = -1;
+  int64_t reg = 0;
+  size_t off_first = 0, off_pairs = 0, off_drawn = 0, off_bcount = 0, off_bcursor = 0, off_ent = 0, off_cols = 0;
   size_t off_hdr = 0, off_inside = 0, off_host = 0, off_ok = 0, off_dest = 0, off_cnt = 0, off_S = 0, off_flags = 0,
          off_pos = 0, off_A = 0, off_Aout = 0, off_C = 0, off_Cout = 0, off_tmp = 0, tmp_bytes = 0, total = 0;
 };
@@ -581,6 +1070,45 @@ int64_t background_slots(const ebtc_gen_spec* s) {
   return (int64_t)std::min(pairs, std::ceil(mu + 8.0 * std::sqrt(mu * (1.0 - s->p)) + 64.0));
 }
 
+// Bins of the binned assembly, or none (P->nb = 0): graphs of at most 2^21 nodes (a word holds a row of the bin
+// and a column) whose bins of at most kBinRows rows and kBinFill expected entries number kBinMax at most, no
+// pattern putting more than a bin's LDS on one bin, regions and their bins within 32 and 31 bits. The others,
+// among them dense graphs of more than kBinFill entries per row, take the sorts.
+void plan_bins(const ebtc_gen_spec* s, GenPlan* P) {
+  const int64_t n = s->n, per = P->cap_bg / s->count, reg = per + s->pattern_edges;
+  if (n > ((int64_t)1 << kBinColBits) || reg < 1 || reg >= (int64_t)1 << 30) return;
+  const double deg = std::max(1.0, 2.0 * (double)per / (double)n);
+  if (deg > kBinFill) return;
+  int64_t nb = 0;
+  int shift = -1;
+  if (s->family == EBTC_GEN_BA) {  // the last rows' bins hold the most rows, 4/3 of the mean
+    nb = (int64_t)std::ceil(std::max(deg * (double)n / kBinFill, (double)n / (0.74 * kBinRows)));
+  } else {
+    shift = 9;
+    static_assert(kBinRows == 1 << 9, "rows of the largest bins");
+    while (shift > 0 && std::ldexp(deg, shift) > kBinFill) --shift;
+    nb = (n + ((int64_t)1 << shift) - 1) >> shift;
+  }
+  if (nb < 1 || nb > kBinMax) return;
+  if (s->pattern_edges > 0) {
+    std::vector<int32_t> load((size_t)nb, 0);
+    auto add = [&](int local) {
+      const double u = (s->targets[local] + 0.5) / (double)n;
+      const int64_t k = shift >= 0 ? s->targets[local] >> shift : (int64_t)(0.5 * (u + std::sqrt(u)) * (double)nb);
+      load[(size_t)std::min(nb - 1, k)] += 1;
+    };
+    for (int q = 0; q < 2 * s->pattern_edges; ++q) add(s->pattern[q]);
+    if (*std::max_element(load.begin(), load.end()) > kBinCap) return;
+  }
+  const int64_t chunk = (int64_t)kBinPairs * kBinThreads;
+  // a launch's threads number less than 2^32
+  if ((reg + chunk - 1) / chunk * s->count * kBinThreads >= (int64_t)1 << 32) return;
+  if (std::max(nb * kBinSort, n + kGenBlock) * s->count >= (int64_t)1 << 32) return;
+  P->nb = (int)nb;
+  P->shift = shift;
+  P->reg = reg;
+}
+
 int make_plan(const ebtc_gen_spec* s, GenPlan* P) {
   int rc = check_spec(s);
   if (rc) return rc;
@@ -605,6 +1133,21 @@ int make_plan(const ebtc_gen_spec* s, GenPlan* P) {
   P->off_dest = take(sizeof(int64_t) * (size_t)s->count);
   P->off_cnt = take(sizeof(int32_t) * rows);
   P->off_S = take(sizeof(int64_t) * rows);
+  plan_bins(s, P);
+  if (P->nb > 0) {
+    const size_t cells = (size_t)s->count * P->nb, slots = (size_t)s->count * P->reg;
+    P->off_first = take(sizeof(int32_t) * ((size_t)P->nb + 1));
+    P->off_drawn = take(sizeof(int32_t) * (size_t)s->count);
+    P->off_bcount = take(sizeof(uint32_t) * cells);
+    P->off_bcursor = take(sizeof(uint32_t) * cells);
+    // the pairs are read for the last time by the scatter, before the sort writes the columns
+    P->off_cols = P->off_pairs = take(sizeof(int2) * slots);
+    P->off_ent = take(sizeof(uint32_t) * 2 * slots);
+    P->tmp_bytes = scan_tmp_bytes((int64_t)rows);
+    P->off_tmp = take(P->tmp_bytes);
+    P->total = off;
+    return EBTC_OK;
+  }
   P->off_flags = take(sizeof(int32_t) * cap);
   P->off_pos = take(sizeof(int64_t) * cap);
   P->off_A = take(sizeof(uint64_t) * cap);
@@ -631,6 +1174,28 @@ GenArgs make_gen_args(const ebtc_gen_spec* s, const GenPlan& P, char* ws) {
   a.per = s->count > 0 ? P.cap_bg / s->count : 0;
   a.inside = s->t > 0 ? (const uint8_t*)(ws + P.off_inside) : nullptr;
   return a;
+}
+
+BinArgs make_bin_args(const GenPlan& P, char* ws) {
+  BinArgs b{};
+  b.first = (const int32_t*)(ws + P.off_first);
+  b.nb = P.nb;
+  b.shift = P.shift;
+  b.reg = P.reg;
+  b.pairs = (int2*)(ws + P.off_pairs);
+  b.drawn = (int32_t*)(ws + P.off_drawn);
+  b.bcount = (uint32_t*)(ws + P.off_bcount);
+  b.bcursor = (uint32_t*)(ws + P.off_bcursor);
+  b.ent = (uint32_t*)(ws + P.off_ent);
+  b.cols = (uint32_t*)(ws + P.off_cols);
+  return b;
+}
+
+// The scatter's LDS: two words per bin, twice six bytes per pair of a chunk; its opt-in.
+size_t scatter_lds(const GenPlan& P) { return 8 * (size_t)P.nb + 12 * (size_t)kBinPairs * kBinThreads; }
+hipError_t prepare_bins(const GenPlan& P) {
+  return hipFuncSetAttribute((const void*)k_bin_scatter, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)scatter_lds(P));
 }
 
 #define GEN_HIP(call)                                                                              \
@@ -680,7 +1245,16 @@ extern "C" int ebtc_generate_count(const ebtc_gen_spec* spec, void* ws, size_t w
   const GenArgs a = make_gen_args(spec, P, w);
   const int n = spec->n;
 
-  GEN_LAUNCH(k_zero_i64, dim3(1), dim3(kGenBlock), 0, s, hdr, (int64_t)kHdrWords);
+  const BinArgs b = make_bin_args(P, w);
+  if (P.nb > 0) {
+    GEN_HIP(prepare_bins(P));
+    const int64_t cells = (int64_t)spec->count * P.nb;
+    GEN_LAUNCH(k_bin_init, dim3(grid(std::max<int64_t>(cells, std::max<int64_t>(P.nb + 1, kHdrWords)))),
+               dim3(kGenBlock), 0, s, b, n, cells, spec->count,
+               spec->family == EBTC_GEN_ER ? 0 : (int32_t)(P.reg - spec->pattern_edges), (int32_t*)(w + P.off_first), hdr);
+  } else {
+    GEN_LAUNCH(k_zero_i64, dim3(1), dim3(kGenBlock), 0, s, hdr, (int64_t)kHdrWords);
+  }
   if (spec->t > 0) {
     // targets and pattern to the device (small; the host arrays may go away after the call)
     std::vector<int32_t> host((size_t)spec->t + 2 * (size_t)spec->pattern_edges);
@@ -693,6 +1267,33 @@ extern "C" int ebtc_generate_count(const ebtc_gen_spec* spec, void* ws, size_t w
     GEN_LAUNCH(k_mark, dim3(1), dim3(kGenBlock), 0, s, (const int32_t*)(w + P.off_host), spec->t,
                (uint8_t*)(w + P.off_inside));
   }
+  if (P.nb > 0) {
+    if (spec->family == EBTC_GEN_ER) {
+      const int wgs = (n + kGenBlock - 1) / kGenBlock;
+      GEN_LAUNCH(k_er_append, dim3((unsigned)((int64_t)wgs * spec->count)), dim3(kGenBlock), 0, s, a, b, wgs);
+    } else if (spec->family == EBTC_GEN_WS) {
+      GEN_LAUNCH(k_ws_edges<int2>, dim3(grid(P.cap_bg)), dim3(kGenBlock), 0, s, a, b.pairs, b.reg);
+    } else {
+      GEN_LAUNCH(k_ba_edges<int2>, dim3(grid(P.cap_bg)), dim3(kGenBlock), 0, s, a, b.pairs, b.reg);
+    }
+    if (spec->pattern_edges > 0) {
+      const int32_t* tg = (const int32_t*)(w + P.off_host);
+      GEN_LAUNCH(k_bin_pattern, dim3(grid((int64_t)spec->count * spec->pattern_edges)), dim3(kGenBlock), 0, s, a, b, tg,
+                 tg + spec->t);
+    }
+    const int pairs = kBinPairs * kBinThreads, chunks = (int)((P.reg + pairs - 1) / pairs), chunks2 = (chunks + 1) / 2;
+    const dim3 cells((unsigned)((int64_t)spec->count * P.nb));
+    GEN_LAUNCH(k_bin_count, dim3((unsigned)((int64_t)chunks2 * spec->count)), dim3(kBinThreads),
+               sizeof(uint32_t) * P.nb, s, a, b, chunks2, hdr);
+    GEN_LAUNCH(k_bin_starts, dim3((unsigned)spec->count), dim3(kBinThreads), 0, s, b);
+    GEN_LAUNCH(k_bin_scatter, dim3((unsigned)((int64_t)chunks * spec->count)), dim3(kBinThreads), scatter_lds(P), s, a,
+               b, chunks);
+    GEN_LAUNCH(k_bin_sort, cells, dim3(kBinSort), 0, s, a, b, cnt);
+    GEN_HIP(scan_i32_i64(tmp, (const int32_t*)cnt, S, P.rows, s));
+    GEN_LAUNCH(k_row_ptr, dim3(grid((int64_t)spec->count * (n + 1))), dim3(kGenBlock), 0, s, (const int32_t*)cnt,
+               (const int64_t*)S, n, spec->count, (const int64_t*)hdr, row_ptr, nnz, (int32_t*)(w + P.off_ok));
+    return EBTC_OK;
+  }
   if (spec->family == EBTC_GEN_ER) {
     GEN_LAUNCH(k_er_rows<false>, dim3(grid(P.rows)), dim3(kGenBlock), 0, s, a, cnt, (const int64_t*)nullptr,
                (uint64_t*)nullptr, (int64_t)0);
@@ -701,9 +1302,9 @@ extern "C" int ebtc_generate_count(const ebtc_gen_spec* spec, void* ws, size_t w
     GEN_LAUNCH(k_er_rows<true>, dim3(grid(P.rows)), dim3(kGenBlock), 0, s, a, cnt, (const int64_t*)S, A, P.cap_bg);
     if (P.cap_bg > 0) GEN_LAUNCH(k_er_tail, dim3(grid(P.cap_bg)), dim3(kGenBlock), 0, s, (const int64_t*)hdr, A, P.cap_bg);
   } else if (spec->family == EBTC_GEN_WS) {
-    GEN_LAUNCH(k_ws_edges, dim3(grid(P.cap_bg)), dim3(kGenBlock), 0, s, a, A);
+    GEN_LAUNCH(k_ws_edges<uint64_t>, dim3(grid(P.cap_bg)), dim3(kGenBlock), 0, s, a, A, (int64_t)0);
   } else {
-    GEN_LAUNCH(k_ba_edges, dim3(grid(P.cap_bg)), dim3(kGenBlock), 0, s, a, A);
+    GEN_LAUNCH(k_ba_edges<uint64_t>, dim3(grid(P.cap_bg)), dim3(kGenBlock), 0, s, a, A, (int64_t)0);
   }
   if (spec->pattern_edges > 0) {
     const int32_t* tg = (const int32_t*)(w + P.off_host);
@@ -747,6 +1348,13 @@ extern "C" int ebtc_generate_fill(const ebtc_gen_spec* spec, void* ws, size_t ws
   char* w = (char*)ws;
   GEN_HIP(hipMemcpyAsync(w + P.off_dest, dest_off, sizeof(int64_t) * (size_t)spec->count, hipMemcpyHostToDevice, s));
   GEN_HIP(hipStreamSynchronize(s));
+  if (P.nb > 0) {
+    GEN_LAUNCH(k_bin_fill, dim3((unsigned)((int64_t)spec->count * P.nb)), dim3(kGenBlock), 0, s,
+               make_gen_args(spec, P, w), make_bin_args(P, w), (const int64_t*)(w + P.off_S),
+               (const int32_t*)(w + P.off_cnt), (const int64_t*)(w + P.off_dest), (const int32_t*)(w + P.off_ok),
+               col_idx);
+    return EBTC_OK;
+  }
   GEN_LAUNCH(k_scatter_cols, dim3(grid(2 * P.cap)), dim3(kGenBlock), 0, s, (const uint64_t*)(w + P.off_Cout),
              (const int64_t*)(w + P.off_hdr), 2 * P.cap, spec->n, (const int64_t*)(w + P.off_S),
              (const int64_t*)(w + P.off_dest), (const int32_t*)(w + P.off_ok), col_idx);
