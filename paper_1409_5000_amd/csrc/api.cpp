@@ -757,15 +757,16 @@ int resolve_schedule(const ebtc_batch* b, const ebtc_opts* o, int* sched) {
 // Lanczos steps for the launches described by (a, nblocks); a.blkmap / a.single_task select the scope.
 // fa: the SpMV launches of each step, one per form of the plan.
 int run_steps(const ebtc_batch* b, const ebtc_opts* o, const LzArgs& a, const std::vector<FArgs>& fa, int64_t nblocks,
-              int64_t first, int64_t count, hipStream_t s, Prof* prof, bool with_start = true) {
+              int64_t first, int64_t count, hipStream_t s, Prof* prof, bool with_start = true, const SharedMat* mat = nullptr) {
   const bool has_val = b->values != nullptr;
   const int steps = o->m > 0 ? o->m : o->m_max;
   // every realization in one row block: dots and update of a step in one launch (one workgroup each)
   const bool one_block = b->n_max <= kRowsPerBlock && o->reorth == 1 && a.window == 0 && steps <= kDotsWindow;
   if (with_start) EBTC_PHASE(prof, EBTC_PHASE_START, launch_start(b->dtype, a, nblocks, s));
   for (int j = 0; j < steps; ++j) {
+    if (mat) EBTC_PHASE(prof, EBTC_PHASE_SPMV, launch_shared_step(b->dtype, has_val, j, a, *mat, b->n_max, s));
     for (const FArgs& x : fa) {
-      if (x.nb == 0 || (j == 0 && x.a.unit_start && x.a.first_in_prepare)) continue;
+      if (mat || x.nb == 0 || (j == 0 && x.a.unit_start && x.a.first_in_prepare)) continue;
       EBTC_PHASE(prof, j == 0 && x.a.unit_start ? EBTC_PHASE_FIRST : EBTC_PHASE_SPMV,
                  launch_spmv_step(b->dtype, has_val, x.sp.lanes, j, x.a, x.nb, s));
     }
@@ -1656,6 +1657,45 @@ ebtc_opts sc_opts(int32_t m) {
   o.spmv = EBTC_SPMV_STREAM;
   return o;
 }
+
+// Workspace of the products formed together (k_shared.hip), after the layout's. None for one process, for small
+// graphs (n=3000, degree 20, 64 processes: 0.64 ms process by process, 0.80 together) and where the packed vectors
+// of 64 processes pass the 32 bits of an element's place.
+constexpr int32_t kSharedNodes = 4096;
+size_t shared_layout(int32_t dtype, int32_t n, int32_t count, size_t off, char* w, SharedMat* q) {
+  const size_t node = shared_stride_bytes(dtype, std::min(count, 64));
+  if (count < 2 || n < kSharedNodes || node * (size_t)n >= ((size_t)1 << 32) - 4096) return off;
+  q->count = count;
+  q->shares = shared_shares(dtype, n);
+  auto take = [&](size_t bytes) {
+    char* p = w + off;
+    off += align_up(bytes);
+    return p;
+  };
+  q->x = take(shared_stride_bytes(dtype, count) * (size_t)n);
+  q->s = (double*)take(sizeof(double) * (size_t)count);
+  q->cut = (int32_t*)take(sizeof(int32_t) * ((size_t)q->shares + 1));
+  q->longs = (int32_t*)take(sizeof(int32_t) * (size_t)n);
+  q->seen = (int32_t*)take(3 * sizeof(int32_t));
+  return off;
+}
+
+// Together or process by process. A few long rows decide at once: the stream form holds up its launch for them
+// (n=300000 Barabasi-Albert, degree 24, two processes: 46.7 ms, together 5.0; where most rows are long, in a dense
+// matrix, no row does). Otherwise by the times per step, measured on gfx950: the stream form's gathers, at the rate
+// of a graph whose neighbours lie close together (500 G/s, FP64 470; a random graph's 185 and 205 are not known
+// beforehand), against a wavefront load per entry (12 cycles of a compute unit, FP64 23, or its bytes at 7.2 TB/s),
+// packing the vectors, and the launches; no less than the longest row takes (60 ns an entry, together 30). n=1e5, degree 20, FP32, random / ring lattice, together against one by one:
+// 8 processes 1.50 / 2.38 and 1.50 / 1.31 ms, 16 processes 1.72 / 4.20 and 1.73 / 2.06.
+bool shared_pays(int32_t dtype, int32_t n, int32_t count, int32_t rows, int32_t entries, int32_t longest) {
+  if (entries < 0 || entries > 0x7fffffff - 256) return false;  // the kernels look a few entries ahead
+  if (rows > 0) return rows <= n / 16;
+  const bool f64 = dtype == EBTC_F64;
+  const double es = f64 ? 8 : 4, bytes = (double)shared_stride_bytes(dtype, count), nnz = entries;
+  const double alone = std::max(nnz * count / (f64 ? 470e9 : 500e9), longest * 60e-9);
+  const double entry = std::max((f64 ? 38e-12 : 19.5e-12) * ((count + 63) / 64), bytes / 7.2e12);
+  return alone > std::max(nnz * entry, longest * 30e-9) + n * (count * es + bytes) / 2.6e12 + 10e-6;
+}
 }  // namespace
 
 int ebtc_subgraph_centrality_ws_bytes(int32_t dtype, int32_t n, int32_t count, int32_t m, size_t* ws_bytes) {
@@ -1666,7 +1706,8 @@ int ebtc_subgraph_centrality_ws_bytes(int32_t dtype, int32_t n, int32_t count, i
   ebtc_batch b;
   shared_batch(b, dtype, n, nullptr, nullptr, nullptr, count);
   const ebtc_opts o = sc_opts(m);
-  *ws_bytes = make_layout(&b, &o, spmv_plan(&b, &o)).total;
+  SharedMat q{};
+  *ws_bytes = shared_layout(dtype, n, count, make_layout(&b, &o, spmv_plan(&b, &o)).total, nullptr, &q);
   return EBTC_OK;
 }
 
@@ -1683,20 +1724,31 @@ int ebtc_subgraph_centrality(int32_t dtype, int32_t n, const int32_t* row_ptr, c
   const ebtc_opts o = sc_opts(m);
   const BatchPlan bp = spmv_plan(&b, &o);
   const Layout L = make_layout(&b, &o, bp);
-  if (ws_bytes < L.total)
-    return fail(EBTC_EWORKSPACE, "workspace of " + std::to_string(ws_bytes) + " bytes, need " + std::to_string(L.total));
+  SharedMat q{};
+  const size_t need = shared_layout(dtype, n, count, L.total, (char*)ws, &q);
+  if (ws_bytes < need)
+    return fail(EBTC_EWORKSPACE, "workspace of " + std::to_string(ws_bytes) + " bytes, need " + std::to_string(need));
   if (((uintptr_t)ws & 255) != 0) return fail(EBTC_EINVAL, "workspace must be 256-byte aligned");
   hipStream_t s = (hipStream_t)stream;
   char* w = (char*)ws;
+  // first, so that it runs beside the host's copies of the tables
+  if (q.count) EBTC_LAUNCH(launch_shared_prepare(row_ptr, q, n, s));
   rc = upload_tables(&b, w, L, bp, s);
   if (rc) return rc;
-  // the task table lives on this call's stack: wait until the copy has read it
-  EBTC_HIP(hipStreamSynchronize(s));
   LzArgs a = make_args(&b, &o, w, L);
   const std::vector<FArgs> fa = form_args(&b, a, w, L, bp);
+  int32_t seen[3] = {0, 0, 0};
+  if (q.count) {
+    q.wstep = b.tasks[1].w_off - b.tasks[0].w_off;
+    EBTC_HIP(hipMemcpyAsync(seen, q.seen, sizeof(seen), hipMemcpyDeviceToHost, s));
+  }
+  // the task table lives on this call's stack: wait until the copy has read it
+  EBTC_HIP(hipStreamSynchronize(s));
+  if (q.count && !shared_pays(dtype, n, count, seen[0], seen[1], seen[2])) q.count = 0;
+  q.rows = seen[0];
   EBTC_LAUNCH(launch_blkmap(a.tasks, b.R, (int32_t*)(w + L.off_blkmap), s));
   EBTC_LAUNCH(launch_start_unit(dtype, a, nodes, L.total_blocks, s));
-  rc = run_steps(&b, &o, a, fa, L.total_blocks, 0, b.R, s, nullptr, false);
+  rc = run_steps(&b, &o, a, fa, L.total_blocks, 0, b.R, s, nullptr, false, q.count ? &q : nullptr);
   if (rc) return rc;
   EBTC_LAUNCH(launch_tridiag_state(a, 0, b.R, 0, 0, m, 1, 0.0, nullptr, nullptr, s));
   EBTC_LAUNCH(launch_sc_out(a.state, a.tasks, nodes, b.R, sc_out, s));

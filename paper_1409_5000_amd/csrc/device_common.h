@@ -10,12 +10,13 @@ constexpr int kWaves = kBlock / 64;
 // Workgroups are dispatched round-robin over the eight XCDs (workgroup id mod 8). Map them so that
 // each XCD walks a contiguous range of logical workgroups: the workgroups of one realization then
 // share one XCD's L2, where the gathered vector v_j stays resident.
-__device__ inline int logical_block() {
-  const int G = gridDim.x, b = blockIdx.x;
+__device__ inline int logical_block(int b, int G) {
   const int x = b & 7, q = b >> 3;
   const int base = G >> 3, rem = G & 7;
   return x * base + (x < rem ? x : rem) + q;
 }
+
+__device__ inline int logical_block() { return logical_block(blockIdx.x, gridDim.x); }
 
 struct Ref {
   int task;

@@ -228,6 +228,24 @@ hipError_t launch_blkmap(const Task* tasks, int64_t R, int32_t* blkmap, hipStrea
 hipError_t launch_row_max(const Task* tasks, const int32_t* row_ptr, int64_t R, int32_t* out, hipStream_t s);
 hipError_t launch_start(int dtype, const LzArgs& a, int64_t nblocks, hipStream_t s);
 // Subgraph centrality: processes started at e_{nodes[r]}, and SC = e^{theta} y_0 per process.
+// Products of processes that share one matrix (k_shared.hip).
+struct SharedMat {
+  int32_t count;    // processes
+  int32_t shares;   // wavefronts' row shares
+  int64_t wstep;    // elements between the processes' product vectors
+  void* x;          // node-major basis vectors: groups of 64 processes, the last group's rows in whole 64 bytes
+  double* s;        // [count] scales of the step; kSharedStopped: the process takes no part
+  int32_t* cut;     // [shares + 1] first rows
+  int32_t* longs;   // [n] long rows
+  int32_t* seen;    // [3] long rows, entries, entries of the longest row
+  int32_t rows;     // long rows, known to the host once the preparation has run
+};
+constexpr double kSharedStopped = -1.0;
+size_t shared_stride_bytes(int dtype, int32_t count);  // bytes of x per node
+int32_t shared_shares(int dtype, int32_t n);
+hipError_t launch_shared_prepare(const int32_t* row_ptr, const SharedMat& q, int32_t n, hipStream_t s);
+hipError_t launch_shared_step(int dtype, bool has_val, int j, const LzArgs& a, const SharedMat& q, int32_t n,
+                              hipStream_t s);
 hipError_t launch_start_unit(int dtype, const LzArgs& a, const int32_t* nodes, int64_t nblocks, hipStream_t s);
 hipError_t launch_sc_out(const RState* state, const Task* tasks, const int32_t* nodes, int64_t count, double* out,
                          hipStream_t s);
