@@ -43,9 +43,65 @@ __device__ inline Ref resolve(const LzArgs& a) {
   return {t, gb - a.tasks[t].blk_begin};
 }
 
+// x of lane ^ M, in registers: quad permutes, a half-row mirror or a rotation of the rows of 16 lanes, and the
+// row swaps (each leaves one register with the even rows, or halves, of x twice and one with the odd ones). The
+// shuffle through the LDS crossbar that it replaces takes about a hundred cycles.
+template <int M>
+__device__ inline int lane_xor32(int x) {
+  static_assert(M == 1 || M == 2 || M == 4 || M == 8 || M == 16 || M == 32, "one bit of the lane");
+  if constexpr (M == 1) return __builtin_amdgcn_update_dpp(0, x, 0xb1, 0xf, 0xf, false);  // quad_perm 1 0 3 2
+  if constexpr (M == 2) return __builtin_amdgcn_update_dpp(0, x, 0x4e, 0xf, 0xf, false);  // quad_perm 2 3 0 1
+  if constexpr (M == 4) {  // lane ^ 7, then ^ 3
+    const int h = __builtin_amdgcn_update_dpp(0, x, 0x141, 0xf, 0xf, false);  // row_half_mirror
+    return __builtin_amdgcn_update_dpp(0, h, 0x1b, 0xf, 0xf, false);          // quad_perm 3 2 1 0
+  }
+  if constexpr (M == 8) return __builtin_amdgcn_update_dpp(0, x, 0x128, 0xf, 0xf, false);  // row_ror:8
+  if constexpr (M == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    return (threadIdx.x & 16) ? (int)r[0] : (int)r[1];
+  }
+  if constexpr (M == 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return (threadIdx.x & 32) ? (int)r[0] : (int)r[1];
+  }
+}
+template <int M>
+__device__ inline double lane_xor(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)lane_xor32<M>((int)(uint32_t)b), hi = (uint32_t)lane_xor32<M>((int)(uint32_t)(b >> 32));
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
+// Lanes without bit M: a + a of lane ^ M; lanes with it: b + b of lane ^ M.
+template <int M>
+__device__ inline double lane_exchange_add(double a, double b, int lane) {
+  if constexpr (M >= 16) {  // the row swaps do the selection themselves
+    const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+    uint32_t lo[2], hi[2];
+    if constexpr (M == 32) {
+      const auto l = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false);
+      const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+      lo[0] = l[0], lo[1] = l[1], hi[0] = h[0], hi[1] = h[1];
+    } else {
+      const auto l = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
+      const auto h = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+      lo[0] = l[0], lo[1] = l[1], hi[0] = h[0], hi[1] = h[1];
+    }
+    return __builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]) +
+           __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
+  } else {
+    const bool up = (lane & M) != 0;
+    return (up ? b : a) + lane_xor<M>(up ? a : b);
+  }
+}
+
 __device__ inline double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  v += lane_xor<32>(v);
+  v += lane_xor<16>(v);
+  v += lane_xor<8>(v);
+  v += lane_xor<4>(v);
+  v += lane_xor<2>(v);
+  v += lane_xor<1>(v);
   return v;
 }
 
@@ -71,15 +127,10 @@ struct ReduceScatter {
   __device__ static inline void run(double* v, int lane) {
     if constexpr (P > 1) {
       constexpr int h = P / 2;
-      const bool up = (lane & M) != 0;
 #pragma unroll
-      for (int k = 0; k < h; ++k) {
-        const double keep = up ? v[k + h] : v[k];
-        const double send = up ? v[k] : v[k + h];
-        v[k] = keep + __shfl_xor(send, M, 64);
-      }
+      for (int k = 0; k < h; ++k) v[k] = lane_exchange_add<M>(v[k], v[k + h], lane);
     } else {
-      v[0] += __shfl_xor(v[0], M, 64);
+      v[0] += lane_xor<M>(v[0]);
     }
     if constexpr (M > 1) ReduceScatter<(P > 1 ? P / 2 : 1), M / 2>::run(v, lane);
   }

@@ -39,7 +39,7 @@ __global__ __launch_bounds__(dots_threads(P, sizeof(T))) void k_dots_step(LzArgs
   const int n = tk.n, r0 = ref.blk * kRowsPerBlock, r1 = min(n, r0 + kRowsPerBlock);
   const T* Vr = (const T*)a.V + tk.vec_off;
   const int lo = window_lo(a, j) + c0;
-  block_dots<T, P, NT, RING>(Vr, n, lo, min(j, lo + P - 1), r0, r1, nullptr, (const T*)a.W + tk.w_off, nullptr,
+  block_dots<T, P, NT, RING>(Vr, n, lo, min(j, lo + P - 1), r0, r1, (const T*)a.W + tk.w_off,
                              a.part + tk.part_off + (size_t)ref.blk * kPartStride + c0, red);
 }
 
@@ -55,8 +55,8 @@ __global__ __launch_bounds__(kBlock) void k_dots_again(LzArgs a, int j, int c0) 
   const int n = tk.n, r0 = ref.blk * kRowsPerBlock, r1 = min(n, r0 + kRowsPerBlock);
   const T* Vr = (const T*)a.V + tk.vec_off;
   const int lo = window_lo(a, j) + c0;
-  block_dots<T, P, kBlock, RING>(Vr, n, lo, min(j, lo + P - 1), r0, r1, nullptr, Vr + vslot(a, j + 1) * n,
-                                 nullptr, a.part + tk.part_off + (size_t)ref.blk * kPartStride + c0, red);
+  block_dots<T, P, kBlock, RING>(Vr, n, lo, min(j, lo + P - 1), r0, r1, Vr + vslot(a, j + 1) * n,
+                                  a.part + tk.part_off + (size_t)ref.blk * kPartStride + c0, red);
 }
 
 
@@ -91,8 +91,8 @@ __global__ __launch_bounds__(kBlock) void k_dots_update_1(LzArgs a, int j) {
   const Task tk = a.tasks[ref.task];
   if (step_skipped(a, a.state + ref.task, j)) return;
   const int n = min(tk.n, kRowsPerBlock);
-  block_dots<T, P, NT, 0, kBlock>((const T*)a.V + tk.vec_off, tk.n, 0, j, 0, n, nullptr, (const T*)a.W + tk.w_off,
-                                  nullptr, a.part + tk.part_off, red_d);
+  block_dots<T, P, NT, 0, kBlock>((const T*)a.V + tk.vec_off, tk.n, 0, j, 0, n, (const T*)a.W + tk.w_off,
+                                  a.part + tk.part_off, red_d);
   __syncthreads();  // the partials stored above (global) are read back by other threads of the workgroup
   update_body<T, P, 0>(a, tk, step_mem<T>(a, tk, ref.task), ref.blk, j, 1, 1, 0, cs, csum, red);
 }

@@ -149,7 +149,7 @@ __device__ inline void spmv_stream_rows(const int32_t* __restrict__ rp, const in
 // slot i % RING (the ring of the memory-bounded form). red: (NT / 64) * P doubles of LDS.
 template <typename T, int P, int NT, int RING, int NREAL = NT>
 __device__ inline void block_dots(const T* __restrict__ Vr, int n, int lo, int j, int r0, int r1,
-                                  const T* wsrc_lds, const T* wsrc_glob, T* wstore, double* part_blk, double* red) {
+                                  const T* wsrc, double* part_blk, double* red) {
   static_assert(P == 2 || P == 8 || P == 16 || P == 32 || P == 64, "lane layout of ReduceScatter");
   static_assert(NT % NREAL == 0 && NREAL % 64 == 0, "virtual thread layout");
   constexpr int RPT = kRowsPerBlock / NT;
@@ -170,8 +170,7 @@ __device__ inline void block_dots(const T* __restrict__ Vr, int n, int lo, int j
     for (int q = 0; q < RPT; ++q) {
       const int r = r0 + q * NT + vt;
       if (r < r1) {
-        const T wv = wsrc_lds ? wsrc_lds[r - r0] : wsrc_glob[r];
-        if (wstore) wstore[r] = wv;
+        const T wv = wsrc[r];
 #pragma unroll
         for (int d0 = 0; d0 < P; d0 += CH) {
           if (d0 < cnt) {
@@ -240,13 +239,10 @@ __device__ inline StepMem<T> step_mem(const LzArgs& a, const Task& tk, int task)
   return {a.state + task, (T*)a.V + tk.vec_off, a.part + tk.part_off, a.npart + tk.part_off / kPartStride};
 }
 
-// wsrc (nullable): where the product w of this step is read instead of the W arena (the single-kernel
-// solve keeps it in LDS); xcopy (nullable): also receives v~_{j+1}[r - r0], the next step's gather
-// source in LDS. The arithmetic of a row is the same for every P >= the window.
+// The arithmetic of a row is the same for every P >= the window.
 template <typename T, int P, int RING>
 __device__ inline void update_body(const LzArgs& a, const Task& tk, const StepMem<T>& mem, int blk, int j, int from_w,
-                                   int final_pass, int second, double* cs, double (*csum)[kMaxChunks], double* red,
-                                   const T* wsrc = nullptr, T* xcopy = nullptr) {
+                                   int final_pass, int second, double* cs, double (*csum)[kMaxChunks], double* red) {
   RState* st = mem.st;
   constexpr int CH = P < 8 ? P : 8;
   const int tid = threadIdx.x, lo = window_lo(a, j), cnt = j - lo + 1;
@@ -283,7 +279,7 @@ __device__ inline void update_body(const LzArgs& a, const Task& tk, const StepMe
   __syncthreads();
   const int n = tk.n, r0 = blk * kRowsPerBlock, r1 = min(n, r0 + kRowsPerBlock);
   T* Vr = mem.V;
-  const T* src = from_w ? (wsrc ? wsrc - r0 : (const T*)a.W + tk.w_off) : Vr + vslot(a, j + 1) * n;
+  const T* src = from_w ? (const T*)a.W + tk.w_off : Vr + vslot(a, j + 1) * n;
   T* dst = Vr + vslot(a, j + 1) * n;
   double nrm = 0.0;
 #pragma unroll
@@ -306,7 +302,6 @@ __device__ inline void update_body(const LzArgs& a, const Task& tk, const StepMe
       }
       const T out = (T)acc;
       dst[r] = out;
-      if (xcopy) xcopy[r - r0] = out;
       nrm += (double)out * (double)out;
     }
   }
@@ -319,27 +314,57 @@ __device__ inline void update_body(const LzArgs& a, const Task& tk, const StepMe
 constexpr int kChebMax = 1 << 16;  // Chebyshev terms of the small exponential (d up to 5e7)
 
 __device__ inline double wave_max(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-  return v;
+  v = fmax(v, lane_xor<32>(v));
+  v = fmax(v, lane_xor<16>(v));
+  v = fmax(v, lane_xor<8>(v));
+  v = fmax(v, lane_xor<4>(v));
+  v = fmax(v, lane_xor<2>(v));
+  return fmax(v, lane_xor<1>(v));
 }
-__device__ inline double wave_min(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
-  return v;
+__device__ inline double wave_min(double v) { return -wave_max(-v); }
+
+// v of the lane before (lane 0: 0) and of the lane after (lane 63: 0), in registers: a few cycles, where a shuffle
+// through the LDS crossbar takes about a hundred.
+template <int CTRL>
+__device__ inline double lane_shift(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xf, 0xf, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+__device__ inline double lane_before(double v) { return lane_shift<0x138>(v); }  // wave_shr:1
+__device__ inline double lane_after(double v) { return lane_shift<0x130>(v); }   // wave_shl:1
+__device__ inline double lane_read(double v, int l) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, l);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), l);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
 }
 
-// Number of eigenvalues of the tridiagonal (a, b) below x.
-__device__ inline int sturm_count(const double* a, const double* b, int k, double x, double pivmin) {
-  double d = a[0] - x;
-  if (fabs(d) < pivmin) d = -pivmin;
-  int cnt = d < 0.0;
-  for (int i = 1; i < k; ++i) {
-    d = (a[i] - x) - b[i - 1] * b[i - 1] / d;
-    if (fabs(d) < pivmin) d = -pivmin;
-    cnt += d < 0.0;
+// True when every eigenvalue of the tridiagonal (a, b) lies below x: the leading principal minors of x I - T are
+// then all positive. Their three-term recurrence has no division, which a ratio of successive minors would put into
+// a chain of k dependent steps. g: a power of two of about 1 / the spectrum's width, so that the factors are at
+// most about 1; the pair is rescaled every eight steps.
+__device__ inline bool above_spectrum(const double* a, const double* b, int k, double x, double g) {
+  double q0 = 1.0, q1 = (x - a[0]) * g;
+  bool above = q1 > 0.0;
+  auto step = [&](int i) {
+    const double s = b[i - 1] * g, u = (x - a[i]) * g;
+    const double q2 = u * q1 - (s * s) * q0;
+    above = above && q2 > 0.0;
+    q0 = q1;
+    q1 = q2;
+  };
+  int i = 1;
+  for (; i + 8 <= k; i += 8) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) step(i + u);
+    const int e = -__builtin_amdgcn_frexp_exp(q1);
+    q0 = __builtin_amdgcn_ldexp(q0, e);
+    q1 = __builtin_amdgcn_ldexp(q1, e);
   }
-  return cnt;
+  for (; i < k; ++i) step(i);
+  return above;
 }
 
 struct ExpvOut {
@@ -349,121 +374,153 @@ struct ExpvOut {
   bool finite;
 };
 
-// a, b: LDS arrays (k diagonal, k-1 off-diagonal entries), k <= 128. Called by all 64 lanes of a
-// wave; lane l owns rows l and l + 64 of T.
-__device__ ExpvOut tridiag_expv_wave(const double* a, const double* b, int k, bool shift) {
+// exp(M) e1 for the tridiagonal M = T - theta I whose spectrum lies in [c - d, c + d] (sc = 1 / d, or 1 for a d that
+// vanishes), the expansion below; lane l owns row l, and row l + 64 when TWO; (ta, tl, tr): the rows of t. One
+// wavefront runs one chain of dependent operations, so every instruction of a term counts: neighbours by register
+// moves, the factors 2 of Clenshaw's recurrence in t, the terms four at a time with one look at their size (470
+// cycles a term with shuffles, branches per term and copies; 130 now).
+template <bool TWO>
+__device__ inline void cheb_exp(double ta_0, double tl_0, double tr_0, double ta_1, double tl_1, double tr_1, double c,
+                                double d, double sc, double top, double& x0, double& x1) {
   const int lane = threadIdx.x & 63;
-  const int q0 = lane, q1 = lane + 64;
-  const double ai0_0 = q0 < k ? a[q0] : 0.0, ai0_1 = q1 < k ? a[q1] : 0.0;
-  const double bl_0 = (q0 >= 1 && q0 < k) ? b[q0 - 1] : 0.0, bl_1 = q1 < k ? b[q1 - 1] : 0.0;
-  const double br_0 = (q0 + 1 < k) ? b[q0] : 0.0, br_1 = (q1 + 1 < k) ? b[q1] : 0.0;
-  double theta = 0.0;
-  if (shift) {
-    if (k == 1) {
-      theta = a[0];
-    } else {
-      const double rad0 = fabs(bl_0) + fabs(br_0), rad1 = fabs(bl_1) + fabs(br_1);
-      double lo = wave_min(fmin(q0 < k ? ai0_0 - rad0 : INFINITY, q1 < k ? ai0_1 - rad1 : INFINITY));
-      double hi = wave_max(fmax(q0 < k ? ai0_0 + rad0 : -INFINITY, q1 < k ? ai0_1 + rad1 : -INFINITY));
-      const double bmax = wave_max(fmax(fabs(br_0), fabs(br_1)));
-      const double pivmin = 1e-290 * fmax(1.0, bmax * bmax);
-      const double eps = 1.1102230246251565e-16;
-      hi += 4.0 * eps * fmax(fabs(hi), fabs(lo)) + pivmin;
-      lo -= 4.0 * eps * fmax(fabs(hi), fabs(lo)) + pivmin;
-      for (int it = 0; it < 40; ++it) {
-        if (hi - lo <= 4.0 * eps * fmax(fabs(lo), fabs(hi)) + 2.0 * pivmin) break;
-        const double w = hi - lo;
-        const double x = (lane == 63) ? hi : lo + w * (double)(lane + 1) * (1.0 / 64.0);
-        const int c = sturm_count(a, b, k, x, pivmin);
-        const unsigned long long mask = __ballot(c == k);
-        const int first = mask ? (__ffsll((long long)mask) - 1) : 63;
-        const double nhi = (first == 63) ? hi : lo + w * (double)(first + 1) * (1.0 / 64.0);
-        const double nlo = (first == 0) ? lo : lo + w * (double)first * (1.0 / 64.0);
-        lo = nlo;
-        hi = nhi;
-      }
-      theta = 0.5 * (lo + hi);
+  const double e0 = lane == 0 ? 1.0 : 0.0;
+  // o += f (t v), for f t given; rows 63 and 64 are neighbours across the lane's two halves
+  auto tmul = [&](double a0, double l0, double r0, double a1, double l1, double r1, double v0, double v1, double& o0,
+                  double& o1) {
+    double dn0 = lane_after(v0);
+    if constexpr (TWO) {
+      const double dn1 = lane_after(v1);
+      double up1 = lane_before(v1);
+      const double row64 = lane_read(v1, 0), row63 = lane_read(v0, 63);
+      dn0 = lane == 63 ? row64 : dn0;
+      up1 = lane == 0 ? row63 : up1;
+      o1 = fma(a1, v1, o1);
+      o1 = fma(l1, up1, o1);
+      o1 = fma(r1, dn1, o1);
     }
+    o0 = fma(a0, v0, o0);
+    o0 = fma(l0, lane_before(v0), o0);
+    o0 = fma(r0, dn0, o0);
+  };
+  if (!(d > 1e-10)) {  // M within 1e-10 of c I: second-order Taylor (error below d^3 / 6)
+    double p0 = 0.0, p1 = 0.0, r0 = 0.0, r1 = 0.0;
+    tmul(ta_0, tl_0, tr_0, ta_1, tl_1, tr_1, e0, 0.0, p0, p1);
+    tmul(ta_0, tl_0, tr_0, ta_1, tl_1, tr_1, p0, p1, r0, r1);
+    const double ec = exp(c);
+    x0 = ec * (e0 + p0 + 0.5 * r0);
+    x1 = ec * (p1 + 0.5 * r1);
+    return;
+  }
+  const int K = __builtin_amdgcn_readfirstlane(min((int)ceil(sqrt(84.0 * d)) + 12, kChebMax));
+  const double a0 = 2.0 * ta_0, l0 = 2.0 * tl_0, r0 = 2.0 * tr_0, a1 = 2.0 * ta_1, l1 = 2.0 * tl_1, r1 = 2.0 * tr_1;
+  const double two0 = 2.0 * e0;
+  // mA, mB: m_k and m_{k+1}; (p, q): b_{k+1} and b_{k+2}; S: the sum of the m so far; f: 2 k
+  double mA = 1e-200, mB = 0.0, S = 0.0, f = 2.0 * K;
+  double p_0 = 0.0, p_1 = 0.0, q_0 = 0.0, q_1 = 0.0;
+  auto term = [&](double& m, double& mn, double& b1_0, double& b1_1, double& b2_0, double& b2_1) {
+    b2_0 = fma(two0, m, -b2_0);
+    b2_1 = -b2_1;
+    tmul(a0, l0, r0, a1, l1, r1, b1_0, b1_1, b2_0, b2_1);
+    S += m;
+    mn = fma(f * sc, m, mn);
+    f -= 2.0;
+  };
+  int kk = K;  // terms k = K .. 1
+  auto rescale = [&] {  // the unnormalised recurrence in range: a term grows it less than 1e12-fold
+    if (__builtin_amdgcn_ballot_w64(mA > 1e150)) {
+      constexpr double z = 0x1p-600;
+      mA *= z, mB *= z, S *= z, p_0 *= z, p_1 *= z, q_0 *= z, q_1 *= z;
+    }
+  };
+  for (; kk >= 4; kk -= 4) {
+    term(mA, mB, p_0, p_1, q_0, q_1);
+    term(mB, mA, q_0, q_1, p_0, p_1);
+    term(mA, mB, p_0, p_1, q_0, q_1);
+    term(mB, mA, q_0, q_1, p_0, p_1);
+    rescale();
+  }
+  if (kk >= 2) {
+    term(mA, mB, p_0, p_1, q_0, q_1);
+    term(mB, mA, q_0, q_1, p_0, p_1);
+    kk -= 2;
+  }
+  if (kk == 1) {
+    term(mA, mB, p_0, p_1, q_0, q_1);
+    const double m = mA, b_0 = p_0, b_1 = p_1;
+    mA = mB, mB = m;
+    p_0 = q_0, p_1 = q_1;
+    q_0 = b_0, q_1 = b_1;
+  }
+  // f = b_0 - t b_1 = m_0 e1 + t b_1 - b_2
+  const double e = top == 0.0 ? 1.0 : exp(top);
+  S = 2.0 * S + mA;
+  double o0 = fma(e0, mA, -q_0), o1 = -q_1;
+  tmul(ta_0, tl_0, tr_0, ta_1, tl_1, tr_1, p_0, p_1, o0, o1);
+  x0 = e * o0 / S;
+  x1 = e * o1 / S;
+}
+
+// a, b: LDS arrays (k diagonal, k-1 off-diagonal entries), k <= 128. Called by all 64 lanes of a
+// wave; lane l owns rows l and l + 64 of T. rough: the caller wants only ynorm and ratios of y's components, which
+// do not depend on the shift: an upper bound of lambda_max within 1/2 takes its place (theta: that bound), one or
+// two of the bisection's eight or nine rounds. It must not lie much further above, where the expansion loses
+// exp(theta - lambda_max) in precision; without a shift the same bound ends the interval.
+// KMAX: k is at most that (64: no second row per lane in the code).
+template <int KMAX = kMLimit>
+__device__ ExpvOut tridiag_expv_wave(const double* a, const double* b, int k, bool shift, bool rough = false) {
+  const int lane = threadIdx.x & 63;
+  k = __builtin_amdgcn_readfirstlane(k);
+  const int q0 = lane, q1 = lane + 64;
+  constexpr bool SECOND = KMAX > 64;
+  const double ai0_0 = q0 < k ? a[q0] : 0.0, ai0_1 = SECOND && q1 < k ? a[q1] : 0.0;
+  const double bl_0 = (q0 >= 1 && q0 < k) ? b[q0 - 1] : 0.0, bl_1 = SECOND && q1 < k ? b[q1 - 1] : 0.0;
+  const double br_0 = (q0 + 1 < k) ? b[q0] : 0.0, br_1 = SECOND && q1 + 1 < k ? b[q1] : 0.0;
+  const double rad0 = fabs(bl_0) + fabs(br_0), rad1 = fabs(bl_1) + fabs(br_1);  // Gershgorin
+  const double low = wave_min(fmin(q0 < k ? ai0_0 - rad0 : INFINITY, SECOND && q1 < k ? ai0_1 - rad1 : INFINITY));
+  const double high = wave_max(fmax(q0 < k ? ai0_0 + rad0 : -INFINITY, SECOND && q1 < k ? ai0_1 + rad1 : -INFINITY));
+  double theta = 0.0, top = 0.0;
+  if (k == 1) {
+    (shift ? theta : top) = a[0];
+  } else {
+    const double eps = 1.1102230246251565e-16;
+    double hi = high + 4.0 * eps * fmax(fabs(high), fabs(low)), lo = low - 4.0 * eps * fmax(fabs(hi), fabs(low));
+    const double g = __builtin_amdgcn_ldexp(1.0, -__builtin_amdgcn_frexp_exp(hi - lo));
+    for (int it = 0; it < 40; ++it) {
+      if (hi - lo <= (rough || !shift ? 0.5 : 0.0) + 4.0 * eps * fmax(fabs(lo), fabs(hi))) break;
+      const double w = hi - lo;
+      const double x = (lane == 63) ? hi : lo + w * (double)(lane + 1) * (1.0 / 64.0);
+      const unsigned long long mask = __ballot(above_spectrum(a, b, k, x, g));
+      const int first = mask ? (__ffsll((long long)mask) - 1) : 63;
+      const double nhi = (first == 63) ? hi : lo + w * (double)(first + 1) * (1.0 / 64.0);
+      const double nlo = (first == 0) ? lo : lo + w * (double)first * (1.0 / 64.0);
+      lo = nlo;
+      hi = nhi;
+    }
+    if (shift) theta = rough ? hi : 0.5 * (lo + hi); else top = hi;
   }
   // y = exp(M) e1, M = T - theta I, by the Chebyshev expansion of exp on [bot, top], an interval that
-  // holds the spectrum of M (Gershgorin; top = 0 when theta = lambda_max): with x = c + d t,
+  // holds the spectrum of M (below by Gershgorin; top = 0 with the shift): with x = c + d t,
   //   exp(x) = e^top (i_0 + 2 sum_{k>=1} i_k T_k(t)),  i_k = e^-d I_k(d)  (I_k modified Bessel),
-  // and i_k falls like e^{-k^2 / 2d}, so sqrt(84 d) + 20 terms reach double precision. The i_k come
+  // and i_k falls like e^{-k^2 / 2d}, so sqrt(84 d) + 12 terms reach double precision (those beyond sum to less
+  // than 3e-20 for every d up to 1e5). The i_k come
   // from Miller's backward recurrence I_{k-1} = I_{k+1} + (2k/d) I_k, unnormalised and in the order
   // Clenshaw's recurrence b_k = c_k e1 + 2 t b_{k+1} - b_{k+2} consumes them, so one backward loop does
   // both and the sum divides by the normalisation sum_k c_k T_k(1) = 1 at the end.
-  const double ai_0 = q0 < k ? ai0_0 - theta : 0.0, ai_1 = q1 < k ? ai0_1 - theta : 0.0;
-  const double lo = wave_min(fmin(q0 < k ? ai_0 - fabs(bl_0) - fabs(br_0) : INFINITY,
-                                  q1 < k ? ai_1 - fabs(bl_1) - fabs(br_1) : INFINITY));
-  const double hi = wave_max(fmax(q0 < k ? ai_0 + fabs(bl_0) + fabs(br_0) : -INFINITY,
-                                  q1 < k ? ai_1 + fabs(bl_1) + fabs(br_1) : -INFINITY));
-  const double top = shift ? 0.0 : hi;
-  const double bot = fmin(lo, top);
+  const double ai_0 = q0 < k ? ai0_0 - theta : 0.0, ai_1 = SECOND && q1 < k ? ai0_1 - theta : 0.0;
+  const double bot = fmin(low - theta, top);
   const double c = 0.5 * (bot + top), d = 0.5 * (top - bot);
   // t = (M - c I) / d, row by row (rows beyond k stay zero: no coupling, no diagonal)
   const double sc = d > 1e-10 ? 1.0 / d : 1.0;
-  const double ta_0 = q0 < k ? (ai_0 - c) * sc : 0.0, ta_1 = q1 < k ? (ai_1 - c) * sc : 0.0;
+  const double ta_0 = q0 < k ? (ai_0 - c) * sc : 0.0, ta_1 = SECOND && q1 < k ? (ai_1 - c) * sc : 0.0;
   const double tl_0 = bl_0 * sc, tl_1 = bl_1 * sc, tr_0 = br_0 * sc, tr_1 = br_1 * sc;
-  // (t v) for the two rows of this lane; rows 63 and 64 are neighbours across the lane's two halves
-  auto tmul = [&](double v0, double v1, double& o0, double& o1) {
-    const double up0 = __shfl_up(v0, 1, 64);
-    const double dn0r = __shfl_down(v0, 1, 64);
-    const double row64 = __shfl(v1, 0, 64);
-    const double up1r = __shfl_up(v1, 1, 64);
-    const double row63 = __shfl(v0, 63, 64);
-    const double dn1 = __shfl_down(v1, 1, 64);
-    const double dn0 = lane == 63 ? row64 : dn0r;
-    const double up1 = lane == 0 ? row63 : up1r;
-    o0 = ta_0 * v0 + tl_0 * up0 + tr_0 * dn0;
-    o1 = ta_1 * v1 + tl_1 * up1 + tr_1 * dn1;
-  };
-  const double e = exp(top);
   double x0, x1;
-  if (!(d > 1e-10)) {  // M within 1e-10 of c I: second-order Taylor (error below d^3 / 6)
-    const double u0 = lane == 0 ? 1.0 : 0.0;
-    double p0, p1, r0, r1;
-    tmul(u0, 0.0, p0, p1);
-    tmul(p0, p1, r0, r1);
-    const double ec = exp(c);
-    x0 = ec * (u0 + p0 + 0.5 * r0);
-    x1 = ec * (p1 + 0.5 * r1);
-  } else {
-    const int K = min((int)ceil(sqrt(84.0 * d)) + 20, kChebMax);
-    double m1 = 0.0, m0 = 1e-200, S = 0.0;
-    double b1_0 = 0.0, b1_1 = 0.0, b2_0 = 0.0, b2_1 = 0.0;  // b_{k+1}, b_{k+2}
-    for (int kk = K + 10; kk >= 0; --kk) {
-      const double ck = kk == 0 ? m0 : 2.0 * m0;
-      S += ck;
-      double t0, t1;
-      tmul(b1_0, b1_1, t0, t1);
-      const double n0 = (lane == 0 ? ck : 0.0) + 2.0 * t0 - b2_0;
-      const double n1 = 2.0 * t1 - b2_1;
-      b2_0 = b1_0;
-      b2_1 = b1_1;
-      b1_0 = n0;
-      b1_1 = n1;
-      if (kk > 0) {
-        const double mn = m1 + (2.0 * kk * sc) * m0;
-        m1 = m0;
-        m0 = mn;
-        if (m0 > 1e200) {  // keep the unnormalised recurrence in range
-          m0 *= 1e-200;
-          m1 *= 1e-200;
-          S *= 1e-200;
-          b1_0 *= 1e-200;
-          b1_1 *= 1e-200;
-          b2_0 *= 1e-200;
-          b2_1 *= 1e-200;
-        }
-      }
-    }
-    double t0, t1;
-    tmul(b2_0, b2_1, t0, t1);  // f = b_0 - t b_1
-    x0 = e * (b1_0 - t0) / S;
-    x1 = e * (b1_1 - t1) / S;
+  if (!SECOND || k <= 64) {
+    cheb_exp<false>(ta_0, tl_0, tr_0, 0.0, 0.0, 0.0, c, d, sc, top, x0, x1);
+  } else if constexpr (SECOND) {
+    cheb_exp<true>(ta_0, tl_0, tr_0, ta_1, tl_1, tr_1, c, d, sc, top, x0, x1);
   }
   x0 = q0 < k ? x0 : 0.0;
-  x1 = q1 < k ? x1 : 0.0;
+  x1 = SECOND && q1 < k ? x1 : 0.0;
   ExpvOut o;
   o.theta = theta;
   o.y0 = x0;
@@ -546,14 +603,15 @@ __device__ inline void tridiag_load(const RState* st, const TriPrep& p, double* 
   }
 }
 
+template <int KMAX = kMLimit>
 __device__ inline void tridiag_finish(const LzArgs& args, RState* st, int64_t r, int mode, int j, const TriPrep& p,
                                       const double* a, const double* b, int shift, double tol, ebtc_diag* diag,
                                       double* ckpt) {
   const int lane = threadIdx.x, k = p.k;
   const double beta_last = p.beta_last;
   int flags = p.flags;
-  const ExpvOut o = tridiag_expv_wave(a, b, k, shift != 0);
-  const double ylast = k <= 64 ? __shfl(o.y0, k - 1, 64) : __shfl(o.y1, k - 65, 64);
+  const ExpvOut o = tridiag_expv_wave<KMAX>(a, b, k, shift != 0, mode == 1);
+  const double ylast = KMAX <= 64 || k <= 64 ? __shfl(o.y0, k - 1, 64) : __shfl(o.y1, k - 65, 64);
   const double est = (o.ynorm > 0.0) ? beta_last * fabs(ylast) / o.ynorm : 0.0;
   if (mode == 1) {
     if (lane == 0) {
