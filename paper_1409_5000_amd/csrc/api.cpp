@@ -1382,10 +1382,11 @@ int ebtc_tune(ebtc_batch* b, const ebtc_opts* o, void* ws, size_t ws_bytes, int3
     }
     // The paneled form (the last candidate) takes the place of the forms whose sums it computes bit for bit. The
     // lane-group and staged forms add a row's products in another order: a batch on which one of those is the
-    // fastest of the others stays on it, so that the paneled form's choice changes no result (staged graphs
-    // of n = 1e4 to 2.5e4 could gain a third: 77 against 56 us at 46 x n=21429, degree 25).
+    // fastest of the others, by more than the 3% that two timings of one form differ by, stays on it, so that the
+    // paneled form's choice changes no result (staged graphs of n = 1e4 to 2.5e4 could gain a third: 77 against
+    // 56 us at 46 x n=21429, degree 25).
     int best = -1;
-    double best_ms = 0.0;
+    double best_ms = 0.0, same_ms = INFINITY;
     for (size_t c = 0; c < cands.size() && rc == EBTC_OK; ++c) {
       const SpmvPlan& p = cands[c].p;
       const BatchPlan bp = one_form(b, p);
@@ -1421,8 +1422,9 @@ int ebtc_tune(ebtc_batch* b, const ebtc_opts* o, void* ws, size_t ws_bytes, int3
       const bool prepared = p.form == EBTC_SPMV_SEGMENTED || p.form == EBTC_SPMV_BALANCED || p.form == EBTC_SPMV_PANELED;
       const double t = t_spmv / kReps + (prepared ? t_prep / spread : 0.0);
       ms[cands[c].slot] = (ms[cands[c].slot] < 0 ? 0.0 : ms[cands[c].slot]) + t;
-      const bool stays = p.form == EBTC_SPMV_PANELED && best >= 0 &&
-                         (cands[best].p.form == EBTC_SPMV_LANE_GROUPS || cands[best].p.form == EBTC_SPMV_LDS_STAGED);
+      const bool other_sums = p.form == EBTC_SPMV_LANE_GROUPS || p.form == EBTC_SPMV_LDS_STAGED;
+      const bool stays = p.form == EBTC_SPMV_PANELED && best >= 0 && best_ms < same_ms / 1.03;
+      if (!other_sums && p.form != EBTC_SPMV_PANELED) same_ms = std::min(same_ms, t);
       if (best < 0 || (t < best_ms && !stays)) {
         best = (int)c;
         best_ms = t;

@@ -35,8 +35,16 @@ __device__ inline bool all_stopped(const LzArgs& a, int j) {
   return a.live != nullptr && j > 0 && a.live[j - 1] == 0;
 }
 
-__device__ inline Ref resolve(const LzArgs& a) {
-  const int lb = logical_block();
+// The same map with every XCD's range walked from its end.
+__device__ inline int logical_block_back() {
+  const int G = gridDim.x, b = blockIdx.x;
+  const int x = b & 7, q = b >> 3;
+  const int base = G >> 3, rem = G & 7, cnt = base + (x < rem ? 1 : 0);
+  return x * base + (x < rem ? x : rem) + cnt - 1 - q;
+}
+
+__device__ inline Ref resolve(const LzArgs& a, bool back = false) {
+  const int lb = back ? logical_block_back() : logical_block();
   if (a.blkmap == nullptr) return {a.single_task, lb};
   const int gb = a.sub_blocks ? a.sub_blocks[lb] : lb;
   const int t = a.blkmap[gb];

@@ -27,8 +27,11 @@ namespace {
 
 // k_dots_step: dot partials of w (written by the SpMV) against the window of Vraw_0..j, from its c0-th
 // vector on (at most P of them: a window wider than kDotsWindow takes one launch per kDotsWindow).
+// Where the bits allow 1024 threads, two workgroups per compute unit: at 70 registers one fits (64 x n=1e5, 30 steps:
+// 2.47 ms, at 64 registers 2.29, 5.4 TB/s).
 template <typename T, int P, int RING>
-__global__ __launch_bounds__(dots_threads(P, sizeof(T))) void k_dots_step(LzArgs a, int j, int c0) {
+__global__ __launch_bounds__(dots_threads(P, sizeof(T)), dots_threads(P, sizeof(T)) == kDotsThreads ? 8 : 1)
+    void k_dots_step(LzArgs a, int j, int c0) {
   if (all_stopped(a, j)) return;
   constexpr int NT = dots_threads(P, sizeof(T));
   __shared__ double red[(NT / 64) * P];
@@ -60,13 +63,17 @@ __global__ __launch_bounds__(kBlock) void k_dots_again(LzArgs a, int j, int c0) 
 }
 
 
+// Walks the row blocks from the last: what the dots read last is still in the last-level cache (64 x n=1e5, 30 steps:
+// 2.82 to 2.57 ms, and the next dots gain as much). Reads of the basis bound it, 5 TB/s; where a realization has
+// hundreds of row blocks the sum of their dot partials, formed by every workgroup, takes a tenth.
+constexpr int kUpdateOcc = 8;  // wavefronts per SIMD, 64 registers
 template <typename T, int P, int RING>
-__global__ __launch_bounds__(kBlock) void k_update(LzArgs a, int j, int from_w, int final_pass, int second) {
+__global__ __launch_bounds__(kBlock, kUpdateOcc) void k_update(LzArgs a, int j, int from_w, int final_pass, int second) {
   if (all_stopped(a, j)) return;
   __shared__ double cs[P];
   __shared__ double csum[P][kMaxChunks];
   __shared__ double red[kWaves];
-  const Ref ref = resolve(a);
+  const Ref ref = resolve(a, true);
   if (step_skipped(a, a.state + ref.task, j)) return;
   const Task tk = a.tasks[ref.task];
   update_body<T, P, RING>(a, tk, step_mem<T>(a, tk, ref.task), ref.blk, j, from_w, final_pass, second, cs, csum,
