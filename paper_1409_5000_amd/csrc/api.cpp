@@ -694,6 +694,7 @@ int prepare_kernels(const BatchPlan& bp) {
     if (sp.pancols > 0) EBTC_HIP(prepare_tile_kernels());
   }
   EBTC_HIP(prepare_solve_kernels());
+  EBTC_HIP(prepare_wide_kernels());
   return EBTC_OK;
 }
 
@@ -743,10 +744,44 @@ bool single_ok(const ebtc_batch* b, const ebtc_opts* o) {
   return b->n_max <= kRowsPerBlock && o->reorth == 1 && stream_bits && steps <= kDotsWindow;
 }
 
-// The schedule a call runs: AUTO takes the single-kernel form where it applies.
+// Whether AUTO takes the solve of a few row blocks per workgroup (k_wide.hip): the conditions of the single-kernel
+// schedule but for the size, and forms with the stream's sums where the batch is tuned.
+constexpr int kSchedWide = 100;  // of AUTO only
+bool wide_pays(const ebtc_batch* b, const ebtc_opts* o) {
+  if (o->spmv != EBTC_SPMV_AUTO && o->spmv != EBTC_SPMV_STREAM) return false;
+  const int steps = o->m > 0 ? o->m : o->m_max;
+  if (o->reorth != 1 || steps > kDotsWindow || !wide_fits(b->dtype, b->n_max)) return false;
+  if (o->spmv == EBTC_SPMV_AUTO)
+    for (const auto& f : b->tuned)
+      if (f[0] == EBTC_SPMV_LANE_GROUPS || f[0] == EBTC_SPMV_LDS_STAGED) return false;
+  // The two schedules' times by what bounds them, fitted to 700 calls on gfx950 (2100 to 9000 nodes, degree 2 to 25,
+  // 1 to 300 realizations, every dtype and option; it never chose the slower by more than 2%). A workgroup alone:
+  // a step's barriers and chains, the basis at 45 GB/s, its entries at 0.11 ns (more with values, and the more
+  // workgroups share the L2); together no faster than the last-level cache, in rounds of 256. Per phase: 10 us per
+  // step of an adaptive run up to its cap, 19 or 24 (FP64) of a fixed one, the basis, the entries at the rate of
+  // close neighbours (long rows, which hold that schedule up, are not known here). An adaptive run's steps: 14.
+  const bool fixed = o->m > 0;
+  const double es = b->dtype == EBTC_F64 ? 8 : 4, val = b->values ? es / 4 : 0.0, R = (double)b->R;
+  const double S = fixed ? o->m : std::min(14, steps), rows = (double)b->total_rows;
+  double entries = 0.0;
+  for (const int64_t z : b->nnz_r) entries += (double)z;
+  const double basis = es * (S + 3.0), z = (double)b->z_max;
+  const double share = 0.8 * std::min(1.0, R / 40.0) * (val > 0 || z > 1e5 ? 1.0 : 0.5);
+  const double alone = (fixed ? 14e-6 : 18e-6) + b->n_max * basis / 45e9 + z * (0.11e-9 + 0.06e-9 * val) * (1.0 + share);
+  const double at_once = std::min(1.0, 256.0 / R);
+  const double shared = at_once * (rows * basis / 4.5e12 + entries * (4.0 + (val > 0 ? es : 0.0)) / 6e12);
+  const double step = std::max(alone, shared);
+  const double wide = R <= 256 ? S * step : S * (R / 256.0 * step + 0.3 * alone);
+  const double phases = (fixed ? S * (es > 4 ? 24e-6 : 19e-6) : steps * 10.2e-6) +
+                        S * (rows * (basis + es) / 4.8e12 + entries / 900e9);
+  return wide < 0.95 * phases;
+}
+
+// The schedule a call runs: AUTO takes a single-kernel form where one applies.
 int resolve_schedule(const ebtc_batch* b, const ebtc_opts* o, int* sched) {
   *sched = o->schedule;
-  if (*sched == EBTC_SCHED_AUTO) *sched = single_ok(b, o) ? EBTC_SCHED_SINGLE : EBTC_SCHED_BATCHED;
+  if (*sched == EBTC_SCHED_AUTO)
+    *sched = single_ok(b, o) ? EBTC_SCHED_SINGLE : wide_pays(b, o) ? kSchedWide : EBTC_SCHED_BATCHED;
   if (*sched == EBTC_SCHED_SINGLE && !single_ok(b, o))
     return fail(EBTC_ENOTSUPPORTED, "the single-kernel schedule needs every n <= " + std::to_string(kRowsPerBlock) +
                                         ", m (or m_max) <= " + std::to_string(kDotsWindow) +
@@ -857,12 +892,17 @@ int enqueue_batched(ebtc_batch* b, const ebtc_opts* o, char* ws, const Layout& L
   a.diag = diag;
   // adaptive m: the checks count the realizations still running, and once none is, the launches of
   // the remaining steps up to the cap return at once
-  if (o->m == 0 && sched != EBTC_SCHED_SINGLE) a.live = (int32_t*)(ws + L.off_live);
+  if (o->m == 0 && sched != EBTC_SCHED_SINGLE && sched != kSchedWide) a.live = (int32_t*)(ws + L.off_live);
   const std::vector<FArgs> fa = form_args(b, a, ws, L, bp);
   EBTC_LAUNCH(launch_blkmap(a.tasks, b->R, (int32_t*)(ws + L.off_blkmap), s));
   const int32_t maxblk = (b->n_max + kRowsPerBlock - 1) / kRowsPerBlock;
-  if (sched == EBTC_SCHED_SINGLE) {
-    EBTC_PHASE(prof, EBTC_PHASE_SOLVE,
+  if (sched == EBTC_SCHED_SINGLE || sched == kSchedWide) {
+    if (sched == kSchedWide)
+      EBTC_PHASE(prof, EBTC_PHASE_SOLVE,
+                 launch_solve_wide(b->dtype, b->values != nullptr, a, b->R, o->m > 0 ? o->m : o->m_max, o->shift,
+                                   o->tol, diag, (double*)ckpt, b->n_max, s));
+    else
+      EBTC_PHASE(prof, EBTC_PHASE_SOLVE,
                launch_solve_1(b->dtype, b->values != nullptr, a, b->R, o->m > 0 ? o->m : o->m_max, o->shift, o->tol,
                               diag, (double*)ckpt, b->n_max, b->z_max, s));
     EBTC_PHASE(prof, EBTC_PHASE_SUM, launch_sum(b->dtype, (const GraphInfo*)(ws + L.off_graphs), b->G, maxblk,

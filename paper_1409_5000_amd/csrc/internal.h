@@ -268,6 +268,11 @@ hipError_t launch_combine(int dtype, const LzArgs& a, int64_t nblocks, hipStream
 // Single-kernel solve (k_solve.hip): `count` realizations (one workgroup each, n <= kRowsPerBlock, the
 // whole basis, one Gram-Schmidt pass) from the start vector to u = beta0 V y, with diag and checkpoint
 // as the final small exponential writes them.
+// Solve of realizations of a few row blocks, a workgroup each (k_wide.hip).
+bool wide_fits(int dtype, int n_max);
+hipError_t prepare_wide_kernels();
+hipError_t launch_solve_wide(int dtype, bool has_val, const LzArgs& a, int64_t count, int steps, int shift, double tol,
+                             ebtc_diag* diag, double* ckpt, int n_max, hipStream_t s);
 hipError_t launch_solve_1(int dtype, bool has_val, const LzArgs& a, int64_t count, int steps, int shift, double tol,
                           ebtc_diag* diag, double* ckpt, int n_max, int64_t z_max, hipStream_t s);
 // Opts the single-kernel solve in to the full LDS; once per process, before any stream capture.
