@@ -50,7 +50,7 @@ enum ebtc_status {
 enum ebtc_dtype { EBTC_F32 = 0, EBTC_F64 = 1 };
 
 enum ebtc_schedule {
-  EBTC_SCHED_AUTO = 0,     /* library picks: SINGLE when the batch allows it, else BATCHED         */
+  EBTC_SCHED_AUTO = 0,     /* library picks: a single-kernel form where one applies, else BATCHED  */
   EBTC_SCHED_PLAIN = 1,    /* one realization at a time: per Lanczos step an SpMV, a Gram-Schmidt dot
                               and an update launch (dots and update are one launch when every
                               realization has at most 2048 nodes), plus a few per realization     */

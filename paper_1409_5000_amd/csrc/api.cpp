@@ -116,9 +116,8 @@ struct ebtc_batch {
   // were built for
   std::vector<FormHost> fh;
   std::string fh_sig;
-  std::vector<int32_t> topk_k;
-  std::vector<int64_t> topk_off;
-  std::vector<int32_t> topk_cgraph, topk_cbegin;  // chunked top-K: each chunk's graph, each graph's first chunk
+  std::vector<char> tables;       // the tasks and graphs of a call, as uploaded
+  std::vector<char> topk_tables;  // ebtc_topk's tables, as uploaded
   std::vector<ExecEntry> execs;
   hipStream_t capture_stream = nullptr;
   // SpMV forms chosen by ebtc_tune (empty = not tuned), used when opts->spmv is EBTC_SPMV_AUTO:
@@ -485,8 +484,12 @@ void fill_tables(ebtc_batch* b, const Layout& L, const BatchPlan& bp) {
 int upload_tables(ebtc_batch* b, char* ws, const Layout& L, const BatchPlan& bp, hipStream_t s) {
   fill_tables(b, L, bp);
   const std::vector<FormHost>& fh = form_host(b, bp);
-  EBTC_HIP(hipMemcpyAsync(ws + L.off_tasks, b->tasks.data(), sizeof(Task) * b->R, hipMemcpyHostToDevice, s));
-  EBTC_HIP(hipMemcpyAsync(ws + L.off_graphs, b->graphs.data(), sizeof(GraphInfo) * b->G, hipMemcpyHostToDevice, s));
+  // tasks and graphs in one copy (each costs a small call about 7 us)
+  const size_t graphs_at = L.off_graphs - L.off_tasks;
+  b->tables.resize(graphs_at + sizeof(GraphInfo) * b->G);
+  std::memcpy(b->tables.data(), b->tasks.data(), sizeof(Task) * b->R);
+  std::memcpy(b->tables.data() + graphs_at, b->graphs.data(), sizeof(GraphInfo) * b->G);
+  EBTC_HIP(hipMemcpyAsync(ws + L.off_tasks, b->tables.data(), b->tables.size(), hipMemcpyHostToDevice, s));
   for (size_t f = 0; f < bp.forms.size(); ++f) {
     const FormLayout& F = L.fl[f];
     if (bp.mixed() && F.blocks > 0)
@@ -894,7 +897,8 @@ int enqueue_batched(ebtc_batch* b, const ebtc_opts* o, char* ws, const Layout& L
   // the remaining steps up to the cap return at once
   if (o->m == 0 && sched != EBTC_SCHED_SINGLE && sched != kSchedWide) a.live = (int32_t*)(ws + L.off_live);
   const std::vector<FArgs> fa = form_args(b, a, ws, L, bp);
-  EBTC_LAUNCH(launch_blkmap(a.tasks, b->R, (int32_t*)(ws + L.off_blkmap), s));
+  if (sched != EBTC_SCHED_SINGLE && sched != kSchedWide)  // those map their workgroups themselves
+    EBTC_LAUNCH(launch_blkmap(a.tasks, b->R, (int32_t*)(ws + L.off_blkmap), s));
   const int32_t maxblk = (b->n_max + kRowsPerBlock - 1) / kRowsPerBlock;
   if (sched == EBTC_SCHED_SINGLE || sched == kSchedWide) {
     if (sched == kSchedWide)
@@ -1817,43 +1821,45 @@ int ebtc_topk(ebtc_batch* b, const void* scores, const int32_t* k_per_graph, int
   ebtc_topk_ws_bytes(b, &need);
   if (ws_bytes < need) return fail(EBTC_EWORKSPACE, "top-k workspace too small");
   if (((uintptr_t)ws & 255) != 0) return fail(EBTC_EINVAL, "workspace must be 256-byte aligned");
-  b->topk_k.assign(k_per_graph, k_per_graph + b->G);
-  b->topk_off.resize(b->G);
+  // one copy of all the tables: the graphs, K and first output slot of each; for the chunked selection (chunks of
+  // kTkChunk scores, graph by graph, a graph's chunks following its node ids) each chunk's graph and each graph's
+  // first chunk
+  const bool chunked = b->n_max >= kTopkMultiMin;
+  const int64_t nchunks = chunked ? topk_chunks(b) : 0;
+  const size_t o1 = align_up(sizeof(GraphInfo) * b->G), o2 = o1 + align_up(sizeof(int32_t) * b->G);
+  const size_t o3 = o2 + align_up(sizeof(int64_t) * b->G);
+  const size_t o4 = o3 + (chunked ? align_up(sizeof(int32_t) * (size_t)nchunks) : 0);
+  const size_t o5 = o4 + (chunked ? align_up(sizeof(int32_t) * ((size_t)b->G + 1)) : 0);
+  b->topk_tables.resize(o5);
+  char* t = b->topk_tables.data();
+  std::memcpy(t, b->graphs.data(), sizeof(GraphInfo) * b->G);
+  std::memcpy(t + o1, k_per_graph, sizeof(int32_t) * b->G);
   int64_t off = 0;
   for (int32_t g = 0; g < b->G; ++g) {
-    const int32_t k = b->topk_k[g];
+    const int32_t k = k_per_graph[g];
     if (k < 0 || k > b->n[g] || k > EBTC_TOPK_LIMIT)
       return fail(k > EBTC_TOPK_LIMIT ? EBTC_ENOTSUPPORTED : EBTC_EINVAL,
                   "graph " + std::to_string(g) + ": K must be in [0, min(n, 4096)]");
-    b->topk_off[g] = off;
+    ((int64_t*)(t + o2))[g] = off;
     off += k;
+  }
+  if (chunked) {
+    int32_t c = 0;
+    for (int32_t g = 0; g < b->G; ++g) {
+      ((int32_t*)(t + o4))[g] = c;
+      const int32_t nc = (b->n[g] + kTkChunk - 1) / kTkChunk;
+      for (int32_t i = 0; i < nc; ++i) ((int32_t*)(t + o3))[c++] = g;
+    }
+    ((int32_t*)(t + o4))[b->G] = c;
   }
   hipStream_t s = (hipStream_t)stream;
   char* w = (char*)ws;
-  const size_t o1 = align_up(sizeof(GraphInfo) * b->G), o2 = o1 + align_up(sizeof(int32_t) * b->G);
-  EBTC_HIP(hipMemcpyAsync(w, b->graphs.data(), sizeof(GraphInfo) * b->G, hipMemcpyHostToDevice, s));
-  EBTC_HIP(hipMemcpyAsync(w + o1, b->topk_k.data(), sizeof(int32_t) * b->G, hipMemcpyHostToDevice, s));
-  EBTC_HIP(hipMemcpyAsync(w + o2, b->topk_off.data(), sizeof(int64_t) * b->G, hipMemcpyHostToDevice, s));
-  const size_t o3 = o2 + align_up(sizeof(int64_t) * b->G);
-  if (b->n_max < kTopkMultiMin) {  // one workgroup per graph
+  EBTC_HIP(hipMemcpyAsync(w, t, o5, hipMemcpyHostToDevice, s));
+  if (!chunked) {  // one workgroup per graph
     EBTC_LAUNCH(launch_topk(b->dtype, (const GraphInfo*)w, b->G, (const int32_t*)(w + o1), (const int64_t*)(w + o2),
                             scores, idx_out, val_out, s));
     return EBTC_OK;
   }
-  // chunks of kTkChunk scores, graph by graph (a graph's chunks follow its node ids)
-  const int64_t nchunks = topk_chunks(b);
-  b->topk_cgraph.resize((size_t)nchunks);
-  b->topk_cbegin.resize((size_t)b->G + 1);
-  int32_t c = 0;
-  for (int32_t g = 0; g < b->G; ++g) {
-    b->topk_cbegin[g] = c;
-    const int32_t nc = (b->n[g] + kTkChunk - 1) / kTkChunk;
-    for (int32_t i = 0; i < nc; ++i) b->topk_cgraph[c++] = g;
-  }
-  b->topk_cbegin[b->G] = c;
-  const size_t o4 = o3 + align_up(sizeof(int32_t) * (size_t)nchunks), o5 = o4 + align_up(sizeof(int32_t) * ((size_t)b->G + 1));
-  EBTC_HIP(hipMemcpyAsync(w + o3, b->topk_cgraph.data(), sizeof(int32_t) * (size_t)nchunks, hipMemcpyHostToDevice, s));
-  EBTC_HIP(hipMemcpyAsync(w + o4, b->topk_cbegin.data(), sizeof(int32_t) * ((size_t)b->G + 1), hipMemcpyHostToDevice, s));
   EBTC_LAUNCH(launch_topk_multi(b->dtype, (const GraphInfo*)w, b->G, (const int32_t*)(w + o1), (const int64_t*)(w + o2),
                                 scores, idx_out, val_out, (const int32_t*)(w + o3), (const int32_t*)(w + o4), nchunks,
                                 w + o5, s));

@@ -278,8 +278,7 @@ __global__ __launch_bounds__(kBlock, kSolveOcc) void k_solve_1(LzArgs a, SolveLd
   __shared__ double part_l[kPartStride];
   __shared__ double npart_l[1];
   __shared__ RState st_l;
-  const Ref ref = resolve(a);  // ref.blk == 0: one row block per realization
-  const int64_t r = __builtin_amdgcn_readfirstlane(ref.task);
+  const int64_t r = logical_block();  // one row block per realization
   // in scalar registers, where the compiler does not put what it loads: the loads of the basis then take their
   // addresses from them
   const Task tk = uniform_task(a.tasks[r]);
