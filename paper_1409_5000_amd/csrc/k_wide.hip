@@ -79,17 +79,17 @@ __device__ inline void wide_spmv(const int* rp_l, const int32_t* __restrict__ ci
         acc += (double)pr;
       }
     }
-    if (k < e1) {
-      int c[8];
-      T v[8];
+    for (; k < e1; k += 4) {
+      int c[4];
+      T v[4];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
+      for (int u = 0; u < 4; ++u) {
         const int e = min(k + u, e1 - 1);
         c[u] = ci[e];
         if constexpr (HAS_VAL) v[u] = va[e];
       }
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
+      for (int u = 0; u < 4; ++u) {
         T pr = xs[c[u]];
         if constexpr (HAS_VAL) pr = v[u] * pr;
         const double t = acc + (double)pr;
