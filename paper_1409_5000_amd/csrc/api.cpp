@@ -559,8 +559,14 @@ BatchPlan spmv_plan(const ebtc_batch* b, const ebtc_opts* o) {
   bp.graph_form = b->tuned_graph;
   for (size_t f = 0; f < b->tuned.size(); ++f) {
     const Members m = members_of(bp, f);
-    bp.forms.push_back(spmv_form(b, b->tuned[f][0], b->tuned[f][1], b->tuned[f][2], o->hub_threshold,
-                                 b->tuned.size() > 1 ? &m : nullptr));
+    const Members* mp = b->tuned.size() > 1 ? &m : nullptr;
+    bp.forms.push_back(spmv_form(b, b->tuned[f][0], b->tuned[f][1], b->tuned[f][2], o->hub_threshold, mp));
+    // The tuner times launches over the whole batch. Under the plain schedule a launch covers one realization: its
+    // tiles leave compute units idle and their preparation is launches of its own. The entry-balanced form computes
+    // the same bits (16 x ER n=1e5, degree 20: 34.1 ms paneled, 15.6 balanced; 2 x n=1e6: 7.7 and 6.6; the other way
+    // round on Barabasi-Albert graphs, 8 x n=1e5: 16.6 and 32.8, which one cannot tell here).
+    if (o->schedule == EBTC_SCHED_PLAIN && bp.forms.back().form == EBTC_SPMV_PANELED)
+      bp.forms.back() = spmv_form(b, EBTC_SPMV_BALANCED, 0, 0, o->hub_threshold, mp);
   }
   return bp;
 }
