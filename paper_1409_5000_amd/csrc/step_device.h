@@ -286,7 +286,7 @@ __device__ inline void update_body(const LzArgs& a, const Task& tk, const StepMe
   // one row 6.02, four 5.73 on half the wavefronts)
   constexpr int RQ = 2;
 #pragma unroll 1
-  for (int q = 0; q < kRowsPerThread; q += RQ) {
+  for (int q = 0; q < kRowsPerThread && r0 + q * kBlock < r1; q += RQ) {
     int row[RQ];
     double acc[RQ];
     int z = 0;  // the coefficients are read anew for every group of rows: held over them they spill
