@@ -274,6 +274,8 @@ int ebtc_tridiag_expv(int32_t count, int32_t k, const double* alpha, const doubl
  *   m              Krylov dimension, 1..EBTC_M_LIMIT
  *   sc_out         device double [count]
  *   ws, ws_bytes   device workspace of ebtc_subgraph_centrality_ws_bytes() bytes, 256-byte aligned
+ *                  (with less, down to the processes' own vectors, their products are formed one by one:
+ *                  the same result, slower)
  * Synchronises `stream` once (after uploading its task table), then enqueues the rest
  * asynchronously. Errors: EINVAL, EWORKSPACE, ENOTSUPPORTED (too many row blocks), EHIP. */
 int ebtc_subgraph_centrality_ws_bytes(int32_t dtype, int32_t n, int32_t count, int32_t m, size_t* ws_bytes);

@@ -1778,8 +1778,9 @@ int ebtc_subgraph_centrality(int32_t dtype, int32_t n, const int32_t* row_ptr, c
   const Layout L = make_layout(&b, &o, bp);
   SharedMat q{};
   const size_t need = shared_layout(dtype, n, count, L.total, (char*)ws, &q);
-  if (ws_bytes < need)
+  if (ws_bytes < L.total)
     return fail(EBTC_EWORKSPACE, "workspace of " + std::to_string(ws_bytes) + " bytes, need " + std::to_string(need));
+  if (ws_bytes < need) q.count = 0;  // room for the processes alone: one by one
   if (((uintptr_t)ws & 255) != 0) return fail(EBTC_EINVAL, "workspace must be 256-byte aligned");
   hipStream_t s = (hipStream_t)stream;
   char* w = (char*)ws;

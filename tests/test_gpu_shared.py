@@ -54,3 +54,26 @@ def test_together_equals_one_by_one(gpu_lib, n, hubs, empty, count, weights, dty
     for i in some:
         one = api().subgraph_centrality(drp, dci, vals, nodes[i:i + 1], m=12, dtype=dtype).cpu().numpy()
         assert got[i].tobytes() == one[0].tobytes(), (i, nodes[i], got[i], one[0])
+
+
+def test_a_workspace_for_the_processes_alone_is_taken(gpu_lib):
+    torch = torch_mod()
+    import ctypes
+
+    from paper_1409_5000_amd import _abi as A
+    n, count, m = 5000, 40, 8
+    rp, ci, _ = graph(n, 11, ((7, 1025),))
+    drp, dci = torch.tensor(rp, device="cuda"), torch.tensor(ci, device="cuda")
+    nd = torch.arange(0, 40 * count, 40, dtype=torch.int32, device="cuda")
+    need = ctypes.c_size_t()
+    assert gpu_lib.ebtc_subgraph_centrality_ws_bytes(A.EBTC_F32, n, count, m, ctypes.byref(need)) == 0
+    got = []
+    for size in (need.value, need.value - 1):
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        out = torch.zeros(count, dtype=torch.float64, device="cuda")
+        args = [ctypes.c_void_p(t.data_ptr()) for t in (drp, dci, nd, out, ws)]
+        assert gpu_lib.ebtc_subgraph_centrality(A.EBTC_F32, n, args[0], args[1], None, count, args[2], m, args[3],
+                                                args[4], size, None) == 0
+        torch.cuda.synchronize()
+        got.append(out.cpu().numpy().tobytes())
+    assert got[0] == got[1]
