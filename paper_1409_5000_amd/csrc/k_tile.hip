@@ -12,9 +12,9 @@
 //          panel, row in the band, rank) and its value.
 // A row belongs to one wave, whose LDS operations execute in order, so its products are added in entry
 // order: the CSR-stream form's sums, bit for bit. Two entries of one row must not meet in one LDS
-// instruction, where the order of the adds is not defined: the sort takes each row's k-th entries of a panel
-// before any (k+1)-th, 64 rows at a time, so that they seldom do, and where they do the entry's rank (the
-// number of its row's earlier entries in its group of 64) puts it in a later add.
+// instruction, where the order of the adds is not defined: the sort places the rows' first entries of a panel
+// before the second ones and so on (kTileClasses), so that they seldom do, and where they do the entry's rank
+// (the number of its row's earlier entries in its group of 64) puts it in a later add.
 // Long rows (kTileHubMin) would fill whole groups, one add per entry; they are listed apart and
 // summed by a few workgroups of the same launch from products staged in LDS, one thread per row.
 //
@@ -40,6 +40,7 @@ constexpr int kTileBands = kTileBandsHost;                    // waves that add 
 constexpr int kTileLoaders = kTileThreads / 64 - kTileBands;  // waves that stage the slices
 constexpr int kTileHubGroups = 64;                            // workgroups of a product that take them
 constexpr int kSortThreads = 512;                             // one band per workgroup of the sort
+constexpr int kTileClasses = 4;  // 2: 1.8 and 1.4 adds per group in the two examples; 6: 1.09 and 1.18
 constexpr int kWin = 16, kWinStride = 17;  // entries of a row staged at a time by the sort, and their stride (odd)
 static_assert((kTileMaxRows + kTileBands - 1) / kTileBands <= 1024, "10 bits of row in the band");
 
@@ -227,16 +228,22 @@ __global__ __launch_bounds__(kBlock) void k_tile_fill(LzArgs a, int t0, int coun
 }
 
 // ------------------------------------------------------------------------------- sort
-// One workgroup per band of a share. Counts the band's entries per panel, then places them, a row per lane
-// and kWin entries of each row staged in LDS at a time: every lane walks its row and takes the next place of
-// each entry's panel (an LDS counter). Which rows' entries stand beside each other varies from run to run,
-// but a row's entries keep their order, and so do the sums; the lanes walk side by side, so that two entries
-// of one row seldom fall in one group of 64 (their rank keeps them apart where they do).
+// One workgroup per band of a share. Counts the band's entries per panel and class (a row's first, second, third
+// and later entries of a panel), then places them, a row per lane and kWin entries of each row staged in LDS at a
+// time: every lane walks its row and takes the next place of each entry's panel and class (an LDS counter). Which
+// rows' entries stand beside each other varies from run to run, but a row's entries keep their order, and so do
+// the sums.
+// The classes keep two entries of one row out of one group of 64: rows with a late first entry of a panel have no
+// early second one, so that even the groups where classes meet seldom hold a row twice. Adds per group for 64 x
+// n=1e5, degree 20: 1.23 (first come, first placed: 1.90); n=4e5, degree 24: 1.17 (2.44).
 // Reads the columns twice and the values once, writes words and values: 20 bytes per weighted entry.
 template <typename T, bool HAS_VAL>
 __global__ __launch_bounds__(kSortThreads) void k_tile_sort(LzArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
-  constexpr int NT = kSortThreads, NW = NT / 64, U = 8;
+  constexpr int NT = kSortThreads, U = 8, K = kTileClasses;
+  // the count's groups of 64 entries overlap by the K - 1 that decide their first entries' classes
+  constexpr int H = K - 1, G = 64 - H, NG = NT / 64 * U, SEG = 4 * NG * G;
+  static_assert(SEG + H <= 32 * NT * kWinStride, "a bit per entry of a segment in s_col");
   __shared__ uint32_t s_col[NT * kWinStride];
   __shared__ T s_val[HAS_VAL ? NT * kWinStride : 1];
   __shared__ int s_first[NT], s_len[NT];
@@ -250,7 +257,7 @@ __global__ __launch_bounds__(kSortThreads) void k_tile_sort(LzArgs a) {
   const int n = tk.n, C = a.pan_cols, S = (n + C - 1) / C, P = a.pan_pmax;
   const float inv = 1.0f / (float)C;
   int* start = (int*)smem;  // [S] first place of each panel in the band
-  int* next = start + P;    // [S] next free place
+  int* next = start + P;    // [K][P] entries, then the next free place, of each class and panel
   const int brows = (share.rows + kTileBands - 1) / kTileBands, r_end = share.r_begin + share.rows;
   const int rb = min(r_end, share.r_begin + band * brows), re = min(r_end, rb + brows);
   const int32_t* rp = a.row_ptr + tk.rowptr_off;
@@ -260,28 +267,45 @@ __global__ __launch_bounds__(kSortThreads) void k_tile_sort(LzArgs a) {
   uint32_t* ent = a.tile_ent + tk.aux_off + e0;
   T* val = HAS_VAL ? (T*)a.tile_val + tk.aux_off + e0 : nullptr;
   const unsigned long long below = (1ull << lane) - 1ull;
-  for (int s = tid; s < S; s += NT) start[s] = 0;
+  for (int i = tid; i < K * P; i += NT) next[i] = 0;
   if (tid == 0) s_bad = 0;
   __syncthreads();
   bool bad = false;
-  // adds (sign) the wave's counted lanes to their panels, one LDS add per run of equal panels
-  auto count = [&](bool ok, int c, int sign) {
+  // adds (sign) the entries of lanes H to 63 to their panels and classes; top: a row's first entry
+  auto count = [&](bool ok, bool top, int c, int sign) {
     const bool in = (unsigned)c < (unsigned)n;
     if (ok && !in) bad = true;
     const int p = ok ? (in ? panel_of(c, C, inv) : S - 1) : -1;
     const int prev = __shfl_up(p, 1, 64);
-    const unsigned long long heads = __ballot(lane == 0 || p != prev);
-    if (ok && ((heads >> lane) & 1ull)) {
-      const unsigned long long above = lane == 63 ? 0ull : heads >> (lane + 1);
-      atomicAdd(&start[p], sign * (above ? __ffsll((long long)above) : 64 - lane));
-    }
+    const unsigned long long heads = __ballot(lane == 0 || top || p != prev);
+    const int k = min((int)__clzll((long long)(heads << (63 - lane))), K - 1);
+    if (ok && lane >= H) atomicAdd(&next[k * P + p], sign);
   };
-  for (int k0 = e0 + w0r; k0 < e1; k0 += NT * U) {  // uniform over the wave
-    int c[U];
+  uint32_t* tops = s_col;  // a bit per entry from H before the segment on: a row's first
+  for (int q0 = 0; q0 < blen; q0 += SEG) {
+    const int words = (min(blen - q0, SEG) + H + 31) / 32;
+    for (int i = tid; i < words; i += NT) tops[i] = 0;
+    __syncthreads();
+    for (int row = rb + tid; row < re; row += NT) {
+      const int i = rp[row] - e0 - q0 + H;
+      if (rp[row + 1] > rp[row] && i >= 0 && i < words * 32) atomicOr(&tops[i >> 5], 1u << (i & 31));
+    }
+    __syncthreads();
+    for (int g0 = (tid >> 6) * U; g0 * G < min(blen - q0, SEG); g0 += NG) {  // uniform over the wave
+      int c[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) c[u] = k0 + u * NT + lane < e1 ? ci[k0 + u * NT + lane] : 0;
+      for (int u = 0; u < U; ++u) {
+        const int i = q0 + (g0 + u) * G + lane - H;
+        c[u] = i >= 0 && i < blen ? ci[e0 + i] : 0;
+      }
 #pragma unroll
-    for (int u = 0; u < U; ++u) count(k0 + u * NT + lane < e1, c[u], 1);
+      for (int u = 0; u < U; ++u) {
+        const int l = (g0 + u) * G + lane, i = q0 + l - H;
+        const bool ok = i >= 0 && i < blen && l < words * 32;
+        count(ok, ok && ((tops[l >> 5] >> (l & 31)) & 1u), c[u], 1);
+      }
+    }
+    __syncthreads();
   }
   // long rows leave the band: their entries are taken off the counts, the rows listed in batches
   for (int r0 = rb + w0r; r0 < re; r0 += NT) {
@@ -302,12 +326,12 @@ __global__ __launch_bounds__(kSortThreads) void k_tile_sort(LzArgs a) {
       const int l = __ffsll((long long)hubs) - 1;
       hubs &= hubs - 1ull;
       const int hl = __builtin_amdgcn_readlane(len, l), hb = rp[r0 + l];
-      for (int k0 = 0; k0 < hl; k0 += 64 * U) {
+      for (int k0 = lane - H; k0 - lane + H < hl; k0 += G * U) {
         int c[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) c[u] = k0 + u * 64 + lane < hl ? ci[hb + k0 + u * 64 + lane] : 0;
+        for (int u = 0; u < U; ++u) c[u] = k0 + u * G >= 0 && k0 + u * G < hl ? ci[hb + k0 + u * G] : 0;
 #pragma unroll
-        for (int u = 0; u < U; ++u) count(k0 + u * 64 + lane < hl, c[u], -1);
+        for (int u = 0; u < U; ++u) count(k0 + u * G >= 0 && k0 + u * G < hl, k0 + u * G == 0, c[u], -1);
       }
       if (sum + hl > TileShape<T>::HCAP) emit();
       ++cnt;
@@ -322,7 +346,13 @@ __global__ __launch_bounds__(kSortThreads) void k_tile_sort(LzArgs a) {
     uint32_t* ends = a.tile_end + ((int64_t)sh * kTileBands + band) * P;
     int run = 0;
     for (int s0 = 0; s0 < S; s0 += 64) {
-      const int s = s0 + lane, v = s < S ? start[s] : 0;
+      const int s = s0 + lane;
+      int f[K], v = 0;  // the classes' first places in the panel
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        f[k] = v;
+        v += s < S ? next[k * P + s] : 0;
+      }
       int inc = v;
 #pragma unroll
       for (int o = 1; o < 64; o <<= 1) {
@@ -330,7 +360,9 @@ __global__ __launch_bounds__(kSortThreads) void k_tile_sort(LzArgs a) {
         if (lane >= o) inc += x;
       }
       if (s < S) {
-        start[s] = next[s] = run + inc - v;
+        start[s] = run + inc - v;
+#pragma unroll
+        for (int k = 0; k < K; ++k) next[k * P + s] = run + inc - v + f[k];
         ends[s] = (uint32_t)(run + inc);
       }
       run += __builtin_amdgcn_readlane(inc, 63);
@@ -352,7 +384,7 @@ __global__ __launch_bounds__(kSortThreads) void k_tile_sort(LzArgs a) {
     const int row = r0 + tid;
     const bool mine = tid < prow && row < re;
     const int b = mine ? rp[row] : 0, full = mine ? rp[row + 1] - b : 0, len = full > hub ? 0 : full;
-    int done = 0, prev = -1, lpan = -1, lgrp = 0, lrank = 0;
+    int done = 0, prev = -1, lpan = -1, lcls = 0, lgrp = 0, lrank = 0;
     double acc = 0.0;
     while (__syncthreads_or(done < len)) {
       const int w = min(len - done, kWin);
@@ -377,8 +409,8 @@ __global__ __launch_bounds__(kSortThreads) void k_tile_sort(LzArgs a) {
           if constexpr (HAS_VAL) val_l[r * kWinStride + o] = v[u];
         }
       }
-      // one entry of every row per round, the waves side by side: the barrier keeps a row's entries of one
-      // panel as many places apart as rows have one there
+      // one entry of every row per round, the waves side by side: the barrier keeps late first entries of a panel
+      // behind early ones
       for (int j = 0; j < kWin; ++j) {
         lds_barrier();
         if (j < w) {
@@ -389,7 +421,9 @@ __global__ __launch_bounds__(kSortThreads) void k_tile_sort(LzArgs a) {
             c = min(max(c, prev), n - 1);
           }
           prev = c;
-          const int s = panel_of(c, C, inv), pos = atomicAdd(&next[s], 1), grp = (pos - start[s]) >> 6;
+          const int s = panel_of(c, C, inv);
+          lcls = lpan == s ? min(lcls + 1, K - 1) : 0;
+          const int pos = atomicAdd(&next[lcls * P + s], 1), grp = (pos - start[s]) >> 6;
           lrank = lpan == s && lgrp == grp ? lrank + 1 : 0;
           lpan = s;
           lgrp = grp;
@@ -772,7 +806,7 @@ template <typename T>
 constexpr size_t tile_lds() {
   return 2 * TileShape<T>::COLS * sizeof(T) + sizeof(double) * (size_t)kTileMaxRows;
 }
-size_t sort_lds(const LzArgs& a) { return 2 * (size_t)a.pan_pmax * sizeof(int); }
+size_t sort_lds(int panels) { return (1 + kTileClasses) * (size_t)panels * sizeof(int); }
 
 template <typename K>
 hipError_t allow(K kernel, size_t dyn) {
@@ -787,7 +821,7 @@ auto tile_kernel(int run_short, F f) {
 
 template <typename T>
 hipError_t prepare_tile_t() {
-  constexpr size_t srt = 2 * (size_t)kTileMaxPanels * sizeof(int);
+  const size_t srt = sort_lds(kTileMaxPanels);
   hipError_t e = hipSuccess;
   for (int r = 0; r < 2; ++r) {
     if (e == hipSuccess) e = tile_kernel<T, true>(r, [](auto k) { return allow(k, tile_lds<T>()); });
@@ -808,7 +842,7 @@ hipError_t tile_prepare_t(const LzArgs& a, int t0, int count, hipStream_t s) {
   hipLaunchKernelGGL(k_tile_pack, dim3(1), dim3(1024), 0, s, a, t0, count, 1);
   hipLaunchKernelGGL(k_tile_fill, dim3((unsigned)((places + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, a, t0, count,
                      places);
-  hipLaunchKernelGGL((k_tile_sort<T, HAS_VAL>), dim3((unsigned)(places * kTileBands)), dim3(kSortThreads), sort_lds(a),
+  hipLaunchKernelGGL((k_tile_sort<T, HAS_VAL>), dim3((unsigned)(places * kTileBands)), dim3(kSortThreads), sort_lds(a.pan_pmax),
                      s, a);
   if constexpr (HAS_VAL) {
     if (a.first_in_prepare)

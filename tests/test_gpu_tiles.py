@@ -109,3 +109,27 @@ def test_adjoint_on_tiles(gpu_lib):
         out = b.scores(m=12, schedule="batched", spmv=form)
         grads.append(b.scores_backward(out.log_scale, g, m=12, spmv=form).cpu().numpy().tobytes())
     assert grads[0] == grads[1]
+
+
+@pytest.mark.parametrize("dtype,values", [("f32", True), ("f32", False), ("f64", True)])
+def test_rows_with_many_entries_per_panel(gpu_lib, dtype, values):
+    # rows of 1 to 250 entries in 1 to 4 neighbouring panels of 1000 columns: every class of entries (1st, 2nd, 3rd,
+    # later ones of a row in a panel), at every place in the count's groups of 61, next to the long rows' limit
+    n = 9000
+    rng = np.random.default_rng(17)
+    parts = []
+    for h in range(0, n, 3):
+        length, at = int(rng.integers(1, 251)), int(rng.integers(0, 5000))
+        parts.append(G.canon(np.full(length, h), at + rng.choice(int(rng.integers(250, 4001)), length, replace=False), n))
+    b = api().Batch.from_csr([[csr(n, np.concatenate(parts), rng, values)] * 3], dtype=dtype)
+    ref = scored(b, m=8, spmv="stream")
+    assert scored(b, m=8, spmv="paneled") == ref
+    assert scored(b, m=8, spmv="paneled", seg_len=1000) == ref
+
+
+def test_bands_longer_than_a_segment_of_the_count(gpu_lib):
+    # 64 realizations of 20000 nodes, degree 50: bands of about 20000 entries, the count's segments hold 15616
+    rng = np.random.default_rng(19)
+    g = csr(20_000, G.er_keys(20_000, 50.0 / 19_999, rng), rng, False)
+    b = api().Batch.from_csr([[g] * 64], dtype="f32")
+    assert scored(b, m=6, spmv="paneled") == scored(b, m=6, spmv="stream")
