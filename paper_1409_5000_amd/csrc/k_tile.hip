@@ -16,17 +16,17 @@
 // before the second ones and so on (kTileClasses), so that they seldom do, and where they do the entry's rank
 // (the number of its row's earlier entries in its group of 64) puts it in a later add.
 // Long rows (kTileHubMin) would fill whole groups, one add per entry; they are listed apart and
-// summed by a few workgroups of the same launch from products staged in LDS, one thread per row.
+// summed by workgroups of their own in the same launch from products staged in LDS, one thread per row.
 //
 // Bound by the entry stream and, for few entries per tile, by the slices. Per product, FP32 (us; before: the
 // fastest other form):
-//   64 x n=1e5, degree 20, values         247   before 336 (column-segmented); its bytes alone take 148
-//   24 x n=99991, degree 15, values        76   before 131 (column-segmented)
-//   16 x n=2e5, degree 16, values         130   before 224 (column-segmented)
-//   8 x n=4e5, degree 24, pattern         175   before 590 (entry-balanced)
-//   8 x n=436472, degree 20, pattern, BA  226   before 520 (entry-balanced)
-//   3 x n=1e6, degree 10, values          211   before 257 (entry-balanced), and 1.2 ms for step 0
-// and 1.1 ms for the sort of the first (128M entries, 20 bytes of traffic each).
+//   64 x n=1e5, degree 20, values         229   before 336 (column-segmented); its bytes alone take 148
+//   24 x n=99991, degree 15, values        72   before 131 (column-segmented)
+//   16 x n=2e5, degree 16, values         115   before 224 (column-segmented)
+//   8 x n=4e5, degree 24, pattern         151   before 590 (entry-balanced)
+//   8 x n=436472, degree 20, pattern, BA  194   before 520 (entry-balanced)
+//   3 x n=1e6, degree 10, values          209   before 257 (entry-balanced), and 1.2 ms for step 0
+// and 1.2 ms for the sort of the first (128M entries, 20 bytes of traffic each).
 #include <algorithm>
 #include <type_traits>
 
@@ -38,7 +38,9 @@ namespace {
 constexpr int kTileThreads = 1024;
 constexpr int kTileBands = kTileBandsHost;                    // waves that add entries
 constexpr int kTileLoaders = kTileThreads / 64 - kTileBands;  // waves that stage the slices
-constexpr int kTileHubGroups = 64;                            // workgroups of a product that take them
+// Workgroups of a product that take the long rows, one per compute unit: 32 took 956 us where 64 took 545 and 256
+// take 505 (24 x n=436472 Barabasi-Albert); where there are none they return at once (64 x n=1e5: 233 us with both).
+constexpr int kTileHubGroups = 256;
 constexpr int kSortThreads = 512;                             // one band per workgroup of the sort
 constexpr int kTileClasses = 4;  // 2: 1.8 and 1.4 adds per group in the two examples; 6: 1.09 and 1.18
 constexpr int kWin = 16, kWinStride = 17;  // entries of a row staged at a time by the sort, and their stride (odd)
@@ -143,8 +145,9 @@ __global__ __launch_bounds__(64) void k_tile_cut(LzArgs a, int t0, int again) {
 // again = 1: the realizations' share counts to offsets in the launch. Before that the rows per share: where
 // shares end early they come on top of the rounds of kTileUnits that the host filled, and a few shares over
 // would cost a whole round, so every share takes more rows, or, at the most a unit holds, one round more is
-// filled (8 x n=436472 Barabasi-Albert: 560 shares of 6821 rows took 3 rounds, 316 us a product, 510 of
-// 7686 take 2, 226 us).
+// filled (8 x n=436472 Barabasi-Albert: 560 shares of 6821 rows took 3 rounds, 316 us a product; two rounds now,
+// 194 us). 15% to spare: such graphs have shares of few, long rows, which take longer (three n=1e6 graphs:
+// 224 us a product with 6%, 209 with 15, 215 with 25).
 __global__ __launch_bounds__(1024) void k_tile_pack(LzArgs a, int t0, int count, int again) {
   __shared__ int wsum[16];
   __shared__ double su[16], sf[16];
@@ -160,7 +163,7 @@ __global__ __launch_bounds__(1024) void k_tile_pack(LzArgs a, int t0, int count,
     if (tid == 0) {
       int rows = a.tile_rows;
       if (used > full) {
-        const double rounds = fmax(1.0, ceil(full / kTileUnits)), need = 1.06 * used * a.tile_rows / kTileUnits;
+        const double rounds = fmax(1.0, ceil(full / kTileUnits)), need = 1.15 * used * a.tile_rows / kTileUnits;
         double r = ceil(need / rounds);
         if (r > kTileMaxRows) r = ceil(need / (rounds + 1.0));
         rows = (int)fmin((double)kTileMaxRows, fmax((double)tile_min_rows(a.tile_rows, (int)rounds), r));
