@@ -47,18 +47,17 @@ __device__ inline int fresh_tid() {
 }
 
 constexpr int kWideRow = 128;  // entries of a row that one thread sums
-constexpr int kWideHubs = 128; // rows beyond the stream form's capacity at most
 
 // w = s_j A v_j: a thread per row, eight entries at a time (their columns with two wide loads; lanes walk rows side by
 // side, so that a line is used again at once); rows of more than kWideRow entries, dealt out row by row to the
-// wavefronts, 64 products at a time through LDS and summed by one lane; rows beyond the stream form's capacity by the
-// workgroup in that form's order (`first`: in entry order, as in the first-product kernels). Each sum in entry order
-// in FP64, products rounded to T first: the stream form's bits. No barriers but for the last kind: chunks of product
-// slots with two each took 2 to 3 us per 3072 entries, 390 us for 351000 entries where this takes 40.
+// wavefronts, 64 products at a time through LDS and summed by one lane. Each sum in entry order in FP64, products
+// rounded to T first: the stream form's bits. Rows beyond the stream form's capacity, any number of them, take that
+// form's other order there: the sums of 256 threads in T, four threads to a lane, reduced wavefront by wavefront
+// (`first`: in entry order like all others, as in the first-product kernels). No barriers: chunks of product slots
+// with two each took 2 to 3 us per 3072 entries, 390 us for 351000 entries where this takes 40.
 template <typename T, bool HAS_VAL>
 __device__ inline void wide_spmv(const int* rp_l, const int32_t* __restrict__ ci, const T* __restrict__ va, const T* xs,
-                                 int n, double sj, T* W, T* prod, double* red, const uint16_t* hubs, int nhub,
-                                 bool first) {
+                                 int n, double sj, T* W, T* prod, bool first) {
   constexpr int CAP = StreamShape<T>::CAP;
   struct __attribute__((packed, aligned(4))) Cols { int32_t c[8]; };
   struct __attribute__((packed, aligned(sizeof(T)))) Vals { T v[8]; };
@@ -102,12 +101,35 @@ __device__ inline void wide_spmv(const int* rp_l, const int32_t* __restrict__ ci
   for (int t = 0; t < n; t += kWideThreads) {
     const int mine = t + lane * kWideWaves + wave;
     const int len = mine < n ? rp_l[mine + 1] - rp_l[mine] : 0;
-    uint64_t m = __ballot(len > kWideRow && len <= CAP);
+    uint64_t m = __ballot(len > kWideRow);
     while (m) {
       const int row = t + __builtin_ctzll(m) * kWideWaves + wave;
       m &= m - 1;
       const int e0 = __builtin_amdgcn_readfirstlane(rp_l[row]), e1 = __builtin_amdgcn_readfirstlane(rp_l[row + 1]);
       double acc = 0.0;
+      if (e1 - e0 > CAP && !first) {
+        T p[4] = {0, 0, 0, 0};
+        for (int k = e0 + lane; k - lane < e1; k += 256) {
+          int c[4];
+          T v[4];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int e = min(k + q * 64, e1 - 1);
+            c[q] = ci[e];
+            if constexpr (HAS_VAL) v[q] = va[e];
+          }
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (k + q * 64 < e1) {
+              const T xv = xs[c[q]];
+              if constexpr (HAS_VAL) p[q] += v[q] * xv; else p[q] += xv;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc += wave_sum((double)p[q]);
+        if (lane == 0) W[row] = (T)(acc * sj);
+        continue;
+      }
       int c = ci[e0 + lane];  // more than 64 entries
       T v = 0;
       if constexpr (HAS_VAL) v = va[e0 + lane];
@@ -137,17 +159,6 @@ __device__ inline void wide_spmv(const int* rp_l, const int32_t* __restrict__ ci
       }
       if (lane == 0) W[row] = (T)(acc * sj);
     }
-  }
-  for (int h = 0; h < nhub; ++h) {
-    const int row = hubs[h];
-    if (first)
-      spmv_stream_rows<T, HAS_VAL, kWideThreads, CAP, true, true, false, kBlock>(nullptr, ci, va, xs, row, 1, sj,
-                                                                                 const_cast<int*>(rp_l) + row, prod,
-                                                                                 W + row, red);
-    else
-      spmv_stream_rows<T, HAS_VAL, kWideThreads, CAP, false, true, false, kBlock>(nullptr, ci, va, xs, row, 1, sj,
-                                                                                  const_cast<int*>(rp_l) + row, prod,
-                                                                                  W + row, red);
   }
 }
 
@@ -197,12 +208,9 @@ __global__ __launch_bounds__(kWideThreads) void k_solve_wide(LzArgs a, WideLds L
   __shared__ double ta[kDotsWindow];
   __shared__ double tb[kDotsWindow];
   __shared__ double nsum[kWideBlocks * 4];
-  __shared__ double red[kWideWaves];
   __shared__ double chunks[kMaxChunks];
   __shared__ double npart_l[1];
   __shared__ RState st_l;
-  __shared__ uint16_t hubs[kWideHubs];
-  __shared__ int nhub;
   constexpr bool F64 = sizeof(T) == 8;
   const int64_t r = blockIdx.x;
   const Task& tk = a.tasks[r];
@@ -227,7 +235,6 @@ __global__ __launch_bounds__(kWideThreads) void k_solve_wide(LzArgs a, WideLds L
   }
   RState* st = &st_l;
   if (tid == 0) {
-    nhub = 0;
     st->beta0 = sqrt((double)n);
     st->s[0] = 1.0 / st->beta0;
     st->theta = 0.0;
@@ -236,9 +243,6 @@ __global__ __launch_bounds__(kWideThreads) void k_solve_wide(LzArgs a, WideLds L
     st->flags = 0;
     st->done = 0;
   }
-  __syncthreads();
-  for (int i = tid; i < n; i += kWideThreads)
-    if (rp_l[i + 1] - rp_l[i] > StreamShape<T>::CAP) hubs[min(atomicAdd(&nhub, 1), kWideHubs - 1)] = (uint16_t)i;
   __syncthreads();
   StepClose c{0.0, 0};  // the last step's, in every thread
   for (int j = 0; j < steps; ++j) {
@@ -250,7 +254,7 @@ __global__ __launch_bounds__(kWideThreads) void k_solve_wide(LzArgs a, WideLds L
       if (c.flags) break;
       sj = 1.0 / c.beta;
     }
-    wide_spmv<T, HAS_VAL>(rp_l, ci, va, xs, n, sj, W, prod, red, hubs, nhub, j == 0);
+    wide_spmv<T, HAS_VAL>(rp_l, ci, va, xs, n, sj, W, prod, j == 0);
     __syncthreads();
     // the dot kernel's thread count for this window (dots_threads of its window class)
     const int cnt = j + 1, P = cnt <= 8 ? 8 : cnt <= 16 ? 16 : cnt <= 32 ? 32 : 64;

@@ -74,3 +74,22 @@ def test_windows_and_breakdown(gpu_lib, dtype):
     b = batch([g] * 140 + [empty], dtype, False)
     for kw in (dict(m=8), dict(m=17), dict(m=33), dict(m=64), dict(m=0, tol=1e-30, m_max=30)):
         check(b, **kw)
+
+
+@pytest.mark.parametrize("dtype,n,cap", [("f64", 10_000, 3072), ("f32", 14_000, 6144)])
+def test_many_rows_beyond_the_capacity(gpu_lib, dtype, n, cap):
+    # 133 rows beyond the stream form's capacity in each of 256 realizations, neighbours among them; no bound on their
+    # number (fixed and adaptive dimension, with the first product's other order)
+    import torch
+    rng = np.random.default_rng(7)
+    lengths = np.full(n, 2)
+    lengths[rng.choice(n - 1, 120, replace=False)] = cap + 1
+    lengths[n // 2:n // 2 + 10] = cap + np.arange(1, 20, 2)
+    lengths[[0, 1, n - 1]] = [cap + 1, cap + 257, cap + 64]
+    rp = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    ci = np.concatenate([np.sort(rng.choice(n, k, replace=False)) for k in lengths]).astype(np.int32)
+    R = 256
+    b = api().Batch([n], [R], np.arange(R) * (n + 1), np.arange(R + 1) * ci.size, torch.as_tensor(rp).cuda().repeat(R),
+                    torch.as_tensor(ci).cuda().repeat(R), None, dtype)
+    check(b, m=8)
+    check(b, m=0, tol=1e-8, m_max=40)
