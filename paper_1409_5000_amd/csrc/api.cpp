@@ -166,6 +166,7 @@ struct SpmvPlan {
   int panask = 0;    // paneled: columns per panel asked for (the limit of 1024 panels counts these)
   int pmax = 0;      // paneled: panels of the largest realization
   int tilerows = 0;  // paneled: rows per share
+  int tileleast = 0;  // paneled: fewest rows per share that the device may choose instead
   int tileshort = 0;  // paneled: a band's runs of entries per panel are short
   // the parameter ebtc_opts::seg_len carries for this form
   int param() const {
@@ -189,7 +190,7 @@ struct BatchPlan {
       t += std::to_string(p.form) + "," + std::to_string(p.lanes) + "," + std::to_string(p.hub) + "," +
            std::to_string(p.seglen) + "," + std::to_string(p.segcols) + "," + std::to_string(p.smax) + "," +
            std::to_string(p.balent) + "," + std::to_string(p.pancols) + "," + std::to_string(p.pmax) + "," +
-           std::to_string(p.tilerows) + "," + std::to_string(p.tileshort) + ";";
+           std::to_string(p.tilerows) + "," + std::to_string(p.tileleast) + "," + std::to_string(p.tileshort) + ";";
     if (mixed())
       for (int32_t f : graph_form) t += std::to_string(f) + ",";
     return t;
@@ -201,7 +202,7 @@ using Members = std::vector<char>;
 bool member(const Members* m, int32_t g) { return m == nullptr || (*m)[g] != 0; }
 
 std::vector<int64_t> bal_shares(const ebtc_batch* b, int e, const Members* m);
-std::vector<int64_t> tile_begins(const ebtc_batch* b, int rows, const Members* m);
+std::vector<int64_t> tile_begins(const ebtc_batch* b, int least, const Members* m);
 
 // Panels per realization at the columns asked for, and the widest panel that may be asked for (the kernels
 // take narrower ones where these exceed their slice buffers).
@@ -224,7 +225,7 @@ int check_form(const ebtc_batch* b, const SpmvPlan& p, const Members* m) {
       return fail(EBTC_EINVAL, "the paneled SpMV takes at most " + std::to_string(kPanelLimit) + " panels: n " +
                                    std::to_string(n_max) + " > " + std::to_string(kPanelLimit) + " x " +
                                    std::to_string(p.panask));
-    if (tile_begins(b, p.tilerows, m).back() > kTileMaxSlots) return fail(EBTC_EINVAL, "too many paneled shares");
+    if (tile_begins(b, p.tileleast, m).back() > kTileMaxSlots) return fail(EBTC_EINVAL, "too many paneled shares");
   }
   if (p.form == EBTC_SPMV_SEGMENTED && p.smax > kSegMax)
     return fail(EBTC_EINVAL, "the column-segmented SpMV needs at most " + std::to_string(kSegMax) +
@@ -280,14 +281,11 @@ int bal_default(const ebtc_batch* b, const Members* m) {
   return e;
 }
 
-// First paneled share slot of each realization ([R + 1]; none for realizations of other forms). rows: what
-// tile_rows chose; the shares may take fewer (tile_min_rows).
-std::vector<int64_t> tile_begins(const ebtc_batch* b, int rows, const Members* m) {
+// First paneled share slot of each realization ([R + 1]; none for realizations of other forms), enough for shares of
+// `least` rows and any larger number (tile_least).
+std::vector<int64_t> tile_begins(const ebtc_batch* b, int least, const Members* m) {
   std::vector<int64_t> v((size_t)b->R + 1, 0);
-  int64_t full = 0, r = 0;
-  for (int32_t g = 0; g < b->G; ++g)
-    if (member(m, g)) full += ((int64_t)b->n[g] + rows - 1) / rows * b->nreal[g];
-  const int least = tile_min_rows(rows, (int)std::min<int64_t>(1 << 20, std::max<int64_t>(1, (full + kTileUnits - 1) / kTileUnits)));
+  int64_t r = 0;
   for (int32_t g = 0; g < b->G; ++g)
     for (int32_t k = 0; k < b->nreal[g]; ++k, ++r)
       v[r + 1] = v[r] + (member(m, g) ? tile_slots(least, b->n[g], b->nnz_r[r]) : 0);
@@ -313,6 +311,16 @@ int tile_rows(const ebtc_batch* b, const Members* m) {
   return lo;
 }
 
+// Fewest rows per share that k_tile_pack may choose where tile_rows chose `rows`: one round of shares more than the
+// batch's. A launch over one realization has fewer rounds, but its slots are the batch's too.
+int tile_least(const ebtc_batch* b, int rows, const Members* m) {
+  int64_t full = 0;
+  for (int32_t g = 0; g < b->G; ++g)
+    if (member(m, g)) full += ((int64_t)b->n[g] + rows - 1) / rows * b->nreal[g];
+  const int64_t rounds = std::min<int64_t>(1 << 20, std::max<int64_t>(1, (full + kTileUnits - 1) / kTileUnits));
+  return (int)((int64_t)rows * rounds / (rounds + 1)) + 1;
+}
+
 // The batch's host tables for plan bp (rebuilt when the plan changes).
 const std::vector<FormHost>& form_host(const ebtc_batch* cb, const BatchPlan& bp) {
   ebtc_batch* b = const_cast<ebtc_batch*>(cb);
@@ -335,7 +343,7 @@ const std::vector<FormHost>& form_host(const ebtc_batch* cb, const BatchPlan& bp
       }
     }
     if (p.form == EBTC_SPMV_BALANCED) h.bal_begin = bal_shares(b, p.balent, mp);
-    if (p.form == EBTC_SPMV_PANELED) h.tile_begin = tile_begins(b, p.tilerows, mp);
+    if (p.form == EBTC_SPMV_PANELED) h.tile_begin = tile_begins(b, p.tileleast, mp);
   }
   b->fh_sig = sig;
   return b->fh;
@@ -527,6 +535,7 @@ SpmvPlan spmv_form(const ebtc_batch* b, int form, int lanes, int seg_len, int hu
     p.pancols = std::min(p.panask, tile_max_cols(b->dtype));
     p.pmax = (n_max + p.pancols - 1) / p.pancols;
     p.tilerows = tile_rows(b, m);
+    p.tileleast = tile_least(b, p.tilerows, m);
     // entries of a band in a panel, over all member realizations: chunks of 384 pay above about 128
     double z = 0.0, runs = 0.0;
     int64_t r = 0;
@@ -641,6 +650,7 @@ std::vector<FArgs> form_args(const ebtc_batch* b, const LzArgs& base, char* ws, 
       a.pan_cols = sp.pancols;
       a.pan_pmax = sp.pmax;
       a.tile_rows = sp.tilerows;
+      a.tile_least = sp.tileleast;
       a.ntile = (int32_t)F.ntile;
       a.tile_begin = (const int64_t*)(ws + F.off_tilebeg);
       a.tile_cut = (TileCut*)(ws + F.off_tilecut);

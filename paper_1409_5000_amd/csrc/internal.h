@@ -107,12 +107,8 @@ __host__ __device__ inline int64_t tile_entries(int rows, int64_t n, int64_t z) 
   const int64_t e = 5 * (int64_t)rows * z / (4 * (n > 0 ? n : 1));
   return e > 8192 ? e : 8192;
 }
-// Fewest rows per share that k_tile_pack may choose where the host chose `rows` for so many rounds.
-__host__ __device__ inline int tile_min_rows(int rows, int rounds) {
-  return (int)((int64_t)rows * rounds / (rounds + 1)) + 1;
-}
-// Shares a realization can be cut into: every share ends by rows or holds, with the next share's first row,
-// more than tile_entries entries, and a row is counted twice at most.
+// Shares a realization can be cut into, `rows` or more rows per share: every share ends by rows or holds, with the
+// next share's first row, more than tile_entries entries, and a row is counted twice at most.
 inline int64_t tile_slots(int rows, int64_t n, int64_t z) {
   return (n + rows - 1) / rows + 2 * z / tile_entries(rows, n, z) + 1;
 }
@@ -192,6 +188,7 @@ struct LzArgs {
   int32_t pan_cols;        // columns per panel
   int32_t pan_pmax;        // most panels of a realization in the launch (the stride of tile_end)
   int32_t tile_rows;       // rows per share at most
+  int32_t tile_least;      // fewest rows per share the slots suffice for (k_tile_pack)
   int32_t ntile;           // share slots of the launch's realizations (its grid)
   const int64_t* tile_begin;  // [R + 1] first share slot of each realization (host-computed)
   TileCut* tile_cut;       // [slots] shares as cut, realization by realization

@@ -145,7 +145,7 @@ __global__ __launch_bounds__(64) void k_tile_cut(LzArgs a, int t0, int again) {
 // again = 1: the realizations' share counts to offsets in the launch. Before that the rows per share: where
 // shares end early they come on top of the rounds of kTileUnits that the host filled, and a few shares over
 // would cost a whole round, so every share takes more rows, or, at the most a unit holds, one round more is
-// filled (8 x n=436472 Barabasi-Albert: 560 shares of 6821 rows took 3 rounds, 316 us a product; two rounds now,
+// filled, and never fewer rows than the host sized the slots for (8 x n=436472 Barabasi-Albert: 560 shares of 6821 rows took 3 rounds, 316 us a product; two rounds now,
 // 194 us). 15% to spare: such graphs have shares of few, long rows, which take longer (three n=1e6 graphs:
 // 224 us a product with 6%, 209 with 15, 215 with 25).
 __global__ __launch_bounds__(1024) void k_tile_pack(LzArgs a, int t0, int count, int again) {
@@ -166,7 +166,7 @@ __global__ __launch_bounds__(1024) void k_tile_pack(LzArgs a, int t0, int count,
         const double rounds = fmax(1.0, ceil(full / kTileUnits)), need = 1.15 * used * a.tile_rows / kTileUnits;
         double r = ceil(need / rounds);
         if (r > kTileMaxRows) r = ceil(need / (rounds + 1.0));
-        rows = (int)fmin((double)kTileMaxRows, fmax((double)tile_min_rows(a.tile_rows, (int)rounds), r));
+        rows = (int)fmin((double)kTileMaxRows, fmax((double)a.tile_least, r));
       }
       a.tile_count[3] = rows;
       a.tile_count[1] = 0;  // long rows
@@ -881,7 +881,7 @@ int64_t tile_hub_rows(int64_t entries) { return entries / (kTileHubMin + 1) + 1;
 
 hipError_t launch_tile_prepare(int dtype, bool has_val, const LzArgs& a, int t0, int count, hipStream_t s) {
   if (a.pan_cols <= 0 || a.pan_cols > tile_max_cols(dtype) || a.pan_pmax < 1 || a.pan_pmax > kTileMaxPanels ||
-      a.tile_rows < 1 || a.tile_rows > kTileMaxRows || a.ntile < 1 || a.ntile > kTileMaxSlots || count < 1)
+      a.tile_rows < 1 || a.tile_rows > kTileMaxRows || a.tile_least < 1 || a.tile_least > a.tile_rows || a.ntile < 1 || a.ntile > kTileMaxSlots || count < 1)
     return hipErrorInvalidValue;
   if (dtype == EBTC_F64)
     return has_val ? tile_prepare_t<double, true>(a, t0, count, s) : tile_prepare_t<double, false>(a, t0, count, s);

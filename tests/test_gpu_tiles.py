@@ -133,3 +133,30 @@ def test_bands_longer_than_a_segment_of_the_count(gpu_lib):
     g = csr(20_000, G.er_keys(20_000, 50.0 / 19_999, rng), rng, False)
     b = api().Batch.from_csr([[g] * 64], dtype="f32")
     assert scored(b, m=6, spmv="paneled") == scored(b, m=6, spmv="stream")
+
+
+@pytest.mark.parametrize("values", [True, False])
+def test_plain_schedule_of_a_batch_of_many_rounds(gpu_lib, values):
+    # 120 realizations of 10 shares: five rounds, so few spare share slots. All entries in 500 or 600 leading rows, long
+    # ones or not, and one realization per launch: the shares are cut anew, and a share without a slot would leave its
+    # rows' products unwritten (the workspace starts as NaN)
+    import torch
+    n, R = 100_000, 120
+    rng = np.random.default_rng(23)
+    for rows, length in ((500, 300), (600, 250)):
+        ci = np.sort(rng.integers(0, n // length, (rows, length)) + np.arange(length) * (n // length), axis=1)
+        rp = np.minimum(np.arange(n + 1), rows) * length
+        va = torch.as_tensor(0.5 + rng.random(rows * length)).cuda().repeat(R) if values else None
+        b = api().Batch([n], [R], np.arange(R) * (n + 1), np.arange(R + 1) * rows * length,
+                        torch.as_tensor(rp.astype(np.int32)).cuda().repeat(R),
+                        torch.as_tensor(ci.astype(np.int32).reshape(-1)).cuda().repeat(R), va, "f32")
+        ref = scored(b, m=4, spmv="stream")
+        for schedule in ("plain", "batched"):
+            run = b.run(m=4, spmv="paneled", schedule=schedule)
+            run.ws.fill_(255)
+            out = run.launch()
+            torch.cuda.synchronize()
+            same = (out.scores.cpu().numpy().tobytes(), out.log_scale.cpu().numpy().tobytes(),
+                    out.diag_numpy().tobytes()) == ref
+            assert same, (rows, schedule)
+            del run, out
