@@ -29,6 +29,14 @@ __device__ inline bool step_skipped(const LzArgs& a, const RState* st, int j) {
   return st->done || (a.stop_mused && j + 1 >= st->m_used);
 }
 
+// The same for the kernels that form step j's product. Their launch also closes step j - 1, and its first workgroup may
+// record a stop while the others start: a stop found by this launch does not count, so that all threads of a workgroup
+// see the same (barriers follow); the closing, which every workgroup does for itself, then ends them.
+__device__ inline bool product_skipped(const LzArgs& a, const RState* st, int j) {
+  const int d = st->done;
+  return (d != 0 && d != 2 + j) || (a.stop_mused && j + 1 >= st->m_used);
+}
+
 // True when every realization of the launch stopped at step j - 1's adaptive check: the launch's
 // workgroups return before reading anything else (the captured sequence runs to the step cap).
 __device__ inline bool all_stopped(const LzArgs& a, int j) {

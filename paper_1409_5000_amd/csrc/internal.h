@@ -137,7 +137,8 @@ struct RState {
   double beta0;            // ||start vector|| = sqrt(n)
   int32_t m_used;
   int32_t flags;
-  int32_t done;            // 1 once the realization stopped (breakdown, estimate met, cap)
+  int32_t done;            // not 0 once the realization stopped (breakdown, estimate met, cap); 2 + j where step
+                           // j's product launch found it (product_skipped)
   int32_t pad0;
 };
 

@@ -634,7 +634,7 @@ __global__ __launch_bounds__(kTileThreads) void k_spmv_tile(LzArgs a, int j) {
   const int task = uniform(share.task);
   if (task < 0) return;
   RState* st = a.state + task;
-  if (step_skipped(a, st, j)) return;
+  if (product_skipped(a, st, j)) return;
   const int n = uniform(share.n), rows = uniform(share.rows), flag = uniform(share.flag), q = uniform(share.q);
   const int C = a.pan_cols, S = (n + C - 1) / C, brows = (rows + kTileBands - 1) / kTileBands;
   const T* x = (const T*)a.V + uniform(share.vec_off) + vslot(a, j) * n;

@@ -9,12 +9,12 @@ namespace ebtc {
 namespace {
 
 // ------------------------------------------------------------------------------- phase A: SpMV
-// Records the close of step j - 1 in the realization's state (one thread).
+// Records the close of step j - 1, by step j's product launch, in the realization's state (one thread).
 __device__ inline void record_close(RState* st, const StepClose& c, int j) {
   st->beta[j - 1] = c.beta;
   if (c.flags) {
     st->flags |= c.flags;
-    st->done = 1;
+    st->done = 2 + j;
     st->m_used = j;
   } else {
     st->s[j] = 1.0 / c.beta;
@@ -26,7 +26,7 @@ __device__ inline void record_close(RState* st, const StepClose& c, int j) {
 // realization is finished; *sj = 1/beta_{j-1} (or s_0 at j = 0).
 __device__ inline bool open_step(const LzArgs& a, const Task& tk, RState* st, int blk, int j, double* chunks,
                                  double* sj, const double* npart = nullptr) {
-  if (step_skipped(a, st, j)) return false;
+  if (product_skipped(a, st, j)) return false;
   if (j == 0) {
     *sj = st->s[0];
     return true;

@@ -160,3 +160,21 @@ def test_plain_schedule_of_a_batch_of_many_rounds(gpu_lib, values):
                     out.diag_numpy().tobytes()) == ref
             assert same, (rows, schedule)
             del run, out
+
+
+def test_breakdown_beside_long_rows_of_others(gpu_lib):
+    # 320 stars (two steps, then breakdown, found by the product launch of the third) between 320 graphs that go on, a
+    # long row or more in each: more batches of long rows than workgroups that take them, stopped ones among them
+    n = 700
+    rng = np.random.default_rng(29)
+    hub = np.arange(1, n)
+    star = G.csr_from_keys(np.unique(G.canon(np.zeros(n - 1, np.int64), hub, n)), n)
+    graphs = []
+    for i in range(320):
+        rows = [(int(h), int(rng.integers(280, 600))) for h in rng.choice(n, 1 + i % 3, replace=False)]
+        graphs += [[star], [csr(n, hubs(n, rows, rng), rng, False)]]
+    b = api().Batch.from_csr(graphs, dtype="f64")
+    for kw in (dict(m=9), dict(m=0, tol=1e-8, m_max=30), dict(m=9, reorth=0)):
+        ref = scored(b, spmv="stream", **kw)
+        same = scored(b, spmv="paneled", **kw) == ref
+        assert same, kw
