@@ -286,16 +286,16 @@ int ebtc_subgraph_centrality(int32_t dtype, int32_t n, const int32_t* row_ptr, c
 /* ---------------------------------------------------------------- autotuning                     */
 /* Chooses the batch's SpMV form by timing. Each graph falls in a bucket given by precision, weights,
  * the octave of n, the half-octave of the mean degree, the octave of the largest row over the mean
- * degree (measured on the device) and the octave of the Krylov steps; the sorted list of the batch's
- * buckets is its composition. Unless the composition is in the process-wide cache (ebtc_tune_cache_*),
+ * degree (measured on the device) and the octave of the Krylov steps that share a preparation (m;
+ * adaptive: m_max, at most 16); the sorted list of the batch's buckets is its composition. Unless the composition is in the process-wide cache (ebtc_tune_cache_*),
  * the forms are timed with HIP events on the whole batch: the CSR stream, lane groups of 4, 8, 16 and
  * 32 lanes per row, the LDS-staged form when the largest vector passes through LDS in at most eight
  * segments, the column-segmented form with 6144 and 12288 FP32 (3072 and 6144 FP64) columns when at
  * most 32 segments, the entry-balanced and the paneled form; each form whose plan fits ws_bytes gets
  * its once-per-call preparation, one warm-up and three timed launches of the first Lanczos product.
- * The fastest per launch, with its preparation spread over the call's m steps (adaptive: 16; the
- * paneled form only in the place of a form with its sums: stream, column-segmented or
- * entry-balanced), is recorded in the cache under the composition and in the batch; later calls with opts->spmv == EBTC_SPMV_AUTO use it
+ * The fastest per launch, with its preparation spread over those steps (the paneled form only in the
+ * place of a form with its sums: stream, column-segmented or entry-balanced), is recorded in the
+ * cache under the composition and in the batch; later calls with opts->spmv == EBTC_SPMV_AUTO use it
  * (a form named in opts overrides it). Plan the later calls after tuning: the chosen form sets their
  * workspace size. Synchronous on the stream. Overwrites the workspace (the largest ebtc_plan size over
  * the forms to try, 256-byte aligned; forms whose plan does not fit are skipped); not thread-safe with
@@ -304,7 +304,7 @@ int ebtc_subgraph_centrality(int32_t dtype, int32_t n, const int32_t* row_ptr, c
  *   ms_out  host [EBTC_TUNE_SLOTS] (nullable): ms per launch of stream, lanes 4, 8, 16, 32,
  *           LDS-staged, column-segmented with 6144 and 12288 FP32 (3072 and 6144 FP64) columns per
  *           segment, entry-balanced and paneled, the segmented, balanced and paneled figures with
- *           their preparation spread over the m steps (-1 where the form was not timed, as for a
+ *           their preparation spread over the steps (-1 where the form was not timed, as for a
  *           composition found in the cache)
  * Errors: EINVAL (NULL batch or workspace, bad opts), EWORKSPACE, EHIP. On error the batch keeps its
  * previous choice. */

@@ -1355,6 +1355,9 @@ int ebtc_tune(ebtc_batch* b, const ebtc_opts* o, void* ws, size_t ws_bytes, int3
   char* w = (char*)ws;
   const bool has_val = b->values != nullptr;
   const int steps = o->m > 0 ? o->m : o->m_max;
+  // Steps that share a preparation: an adaptive run stops long before its cap (12 to 22 steps on the families here).
+  // The cache's key holds them, and not the cap: calls of one key weigh the preparations alike.
+  const int spread = o->m > 0 ? steps : std::min(steps, 16);
   rc = upload_tables(b, w, L, base, s);
   if (rc) return rc;
   // 1. each graph's bucket: its largest row (over its realizations) measured on the device, in the
@@ -1377,7 +1380,7 @@ int ebtc_tune(ebtc_batch* b, const ebtc_opts* o, void* ws, size_t ws_bytes, int3
         mx = std::max(mx, row_max[r]);
       }
       gkey[g] = tune_key(b->dtype, has_val, b->n[g], (double)z / std::max<int64_t>(1, (int64_t)b->nreal[g] * b->n[g]),
-                         mx, steps);
+                         mx, spread);
     }
   }
   // the batch's composition: its buckets, sorted and joined (the cache key of the batch's form)
@@ -1404,8 +1407,6 @@ int ebtc_tune(ebtc_batch* b, const ebtc_opts* o, void* ws, size_t ws_bytes, int3
   }
   std::map<std::string, std::array<int32_t, 3>> choice;
   constexpr int kReps = 3;
-  // Steps that share a preparation: an adaptive run stops long before its cap (12 to 22 steps on the families here).
-  const int spread = o->m > 0 ? steps : std::min(steps, 16);
   for (const std::string& key : keys) {
     {
       std::lock_guard<std::mutex> lock(g_tune_mu);

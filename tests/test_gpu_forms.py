@@ -152,3 +152,18 @@ def test_mixed_forms_refused(gpu_lib):
     b.set_forms(["balanced"] * 6)
     ref = outputs(b, m=16, schedule="batched", spmv="stream")
     assert outputs(b, m=16, schedule="batched") == ref
+
+
+def test_tuner_keys_a_composition_by_the_steps_that_share_a_preparation(gpu_lib):
+    # an adaptive run up to 60 steps weighs a preparation over 16, a fixed m of 60 over 60: neither takes the other's
+    # choice from the cache; a fixed m of 16 and another cap weigh it as the adaptive run does
+    _api = api()
+    b = _api.Batch.from_host(six_graphs("f32", True, N=1, sizes=(12000, 9001, 15000, 5000, 7001, 3000)))
+    for first, second in ((dict(m=60), dict(m=0, m_max=60)), (dict(m=0, m_max=60), dict(m=60))):
+        _api.tune_cache_clear()
+        b.tune(**first)
+        assert b.tune(**second)["ms_per_launch"], (first, second)
+        assert len(_api.tune_cache_text().splitlines()) == 2
+    assert b.tune(m=16)["ms_per_launch"] == {} and b.tune(m=0, m_max=40)["ms_per_launch"] == {}
+    assert b.tune(m=0, m_max=7)["ms_per_launch"]  # fewer steps than 16
+    _api.tune_cache_clear()
