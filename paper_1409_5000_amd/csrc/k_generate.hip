@@ -1191,11 +1191,13 @@ BinArgs make_bin_args(const GenPlan& P, char* ws) {
   return b;
 }
 
-// The scatter's LDS: two words per bin, twice six bytes per pair of a chunk; its opt-in.
-size_t scatter_lds(const GenPlan& P) { return 8 * (size_t)P.nb + 12 * (size_t)kBinPairs * kBinThreads; }
-hipError_t prepare_bins(const GenPlan& P) {
+// The scatter's LDS: two words per bin, twice six bytes per pair of a chunk. Its opt-in is for the most
+// bins, whatever the call's: to this call's size it could take back what another thread's larger call is about to
+// launch with.
+constexpr size_t scatter_lds(int bins) { return 8 * (size_t)bins + 12 * (size_t)kBinPairs * kBinThreads; }
+hipError_t prepare_bins() {
   return hipFuncSetAttribute((const void*)k_bin_scatter, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)scatter_lds(P));
+                             (int)scatter_lds(kBinMax));
 }
 
 #define GEN_HIP(call)                                                                              \
@@ -1247,7 +1249,7 @@ extern "C" int ebtc_generate_count(const ebtc_gen_spec* spec, void* ws, size_t w
 
   const BinArgs b = make_bin_args(P, w);
   if (P.nb > 0) {
-    GEN_HIP(prepare_bins(P));
+    GEN_HIP(prepare_bins());
     const int64_t cells = (int64_t)spec->count * P.nb;
     GEN_LAUNCH(k_bin_init, dim3(grid(std::max<int64_t>(cells, std::max<int64_t>(P.nb + 1, kHdrWords)))),
                dim3(kGenBlock), 0, s, b, n, cells, spec->count,
@@ -1286,7 +1288,7 @@ extern "C" int ebtc_generate_count(const ebtc_gen_spec* spec, void* ws, size_t w
     GEN_LAUNCH(k_bin_count, dim3((unsigned)((int64_t)chunks2 * spec->count)), dim3(kBinThreads),
                sizeof(uint32_t) * P.nb, s, a, b, chunks2, hdr);
     GEN_LAUNCH(k_bin_starts, dim3((unsigned)spec->count), dim3(kBinThreads), 0, s, b);
-    GEN_LAUNCH(k_bin_scatter, dim3((unsigned)((int64_t)chunks * spec->count)), dim3(kBinThreads), scatter_lds(P), s, a,
+    GEN_LAUNCH(k_bin_scatter, dim3((unsigned)((int64_t)chunks * spec->count)), dim3(kBinThreads), scatter_lds(P.nb), s, a,
                b, chunks);
     GEN_LAUNCH(k_bin_sort, cells, dim3(kBinSort), 0, s, a, b, cnt);
     GEN_HIP(scan_i32_i64(tmp, (const int32_t*)cnt, S, P.rows, s));

@@ -48,3 +48,34 @@ def test_bins_bitwise(gpu_lib, family, n, count, binned, kw):
     per = {"er": kw.get("p", 0) * n * (n - 1) / 2, "ws": n * kw.get("k", 0) / 2, "ba": n * kw.get("k", 0)}[family]
     slots = count * (per + len(kw.get("pattern", ())))
     assert (ws.value < 12 * n * count + 32 * slots + 100_000) == binned
+
+
+def test_two_threads_draw_graphs_of_different_sizes(gpu_lib):
+    # 4096 bins need more than 64 KB of the scatter's LDS, one bin does not: each thread's launches take their own size
+    import threading
+    import torch
+    specs = [dict(family="er", n=2 ** 21, count=1, seed=SEED, p=2.0 ** -20), dict(family="er", n=300, count=1, seed=SEED, p=0.1)]
+
+    def draw(spec):
+        rp, ci, nnz = api().generate(**spec)
+        torch.cuda.current_stream().synchronize()
+        return rp.cpu().numpy().tobytes(), ci.cpu().numpy().tobytes(), np.asarray(nnz).tolist()
+
+    ref = [draw(s) for s in specs]
+    wrong = []
+
+    def loop(i):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                for _ in range(60):
+                    if draw(specs[i]) != ref[i]:
+                        wrong.append((i, "another graph"))
+        except Exception as e:
+            wrong.append((i, str(e)))
+
+    threads = [threading.Thread(target=loop, args=(i,)) for i in (0, 1, 1)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
