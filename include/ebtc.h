@@ -53,7 +53,9 @@ enum ebtc_schedule {
   EBTC_SCHED_AUTO = 0,     /* library picks: a single-kernel form where one applies, else BATCHED  */
   EBTC_SCHED_PLAIN = 1,    /* one realization at a time: per Lanczos step an SpMV, a Gram-Schmidt dot
                               and an update launch (dots and update are one launch when every
-                              realization has at most 2048 nodes), plus a few per realization     */
+                              realization has at most 2048 nodes), plus a few per realization. A
+                              recorded paneled form (ebtc_tune) gives way to the entry-balanced
+                              one, whose results are the same bits                                 */
   EBTC_SCHED_BATCHED = 2,  /* all realizations of all graphs advance together, one launch per
                               Lanczos phase, optionally replayed from a captured hipGraph          */
   EBTC_SCHED_SINGLE = 3    /* all realizations in one launch, one workgroup running each
@@ -173,7 +175,8 @@ int ebtc_batch_create(const ebtc_batch_desc* desc, ebtc_batch** out);
 void ebtc_batch_destroy(ebtc_batch* batch);
 
 /* Host-only. Workspace bytes ebtc_scores needs for `opts` (all realizations resident), and the
- * checkpoint bytes ebtc_scores_backward needs (0 if not requested). Also validates opts. */
+ * checkpoint bytes ebtc_scores_backward needs (0 if not requested). The size does not depend on the
+ * schedule. Also validates opts. */
 int ebtc_plan(ebtc_batch* batch, const ebtc_opts* opts, size_t* ws_bytes, size_t* ckpt_bytes);
 
 /* ---------------------------------------------------------------- forward                        */
@@ -197,7 +200,8 @@ int ebtc_scores(ebtc_batch* batch, const ebtc_opts* opts, void* ws, size_t ws_by
  * eager (use_hipgraph is ignored; instantiating a graph would allocate), and the array's device address
  * is looked up once per GPU on the first call there. Arguments, outputs, results and errors as for
  * ebtc_scores, plus EBTC_EWORKSPACE when ebtc_plan's size for (batch, opts) exceeds the array (nothing
- * is enqueued then). Every call on one GPU uses that GPU's one array: calls that overlap on a GPU
+ * is enqueued then). Where that is the size of a recorded paneled form (ebtc_tune) and the
+ * entry-balanced one fits, that one runs. Every call on one GPU uses that GPU's one array: calls that overlap on a GPU
  * (other threads, other streams, or a second call enqueued before the first has run on another
  * stream) race and give undefined results; calls in order on one stream do not. */
 #define EBTC_NOALLOC_WS_BYTES ((size_t)64 << 20)

@@ -570,14 +570,29 @@ BatchPlan spmv_plan(const ebtc_batch* b, const ebtc_opts* o) {
     const Members m = members_of(bp, f);
     const Members* mp = b->tuned.size() > 1 ? &m : nullptr;
     bp.forms.push_back(spmv_form(b, b->tuned[f][0], b->tuned[f][1], b->tuned[f][2], o->hub_threshold, mp));
-    // The tuner times launches over the whole batch. Under the plain schedule a launch covers one realization: its
-    // tiles leave compute units idle and their preparation is launches of its own. The entry-balanced form computes
-    // the same bits (16 x ER n=1e5, degree 20: 34.1 ms paneled, 15.6 balanced; 2 x n=1e6: 7.7 and 6.6; the other way
-    // round on Barabasi-Albert graphs, 8 x n=1e5: 16.6 and 32.8, which one cannot tell here).
-    if (o->schedule == EBTC_SCHED_PLAIN && bp.forms.back().form == EBTC_SPMV_PANELED)
-      bp.forms.back() = spmv_form(b, EBTC_SPMV_BALANCED, 0, 0, o->hub_threshold, mp);
   }
   return bp;
+}
+
+// The plan with the entry-balanced form in the place of a recorded paneled one (a form named in the options stays):
+// the same bits with less memory.
+BatchPlan balanced_plan(const ebtc_batch* b, const ebtc_opts* o) {
+  BatchPlan bp = spmv_plan(b, o);
+  if (o->spmv != EBTC_SPMV_AUTO) return bp;
+  for (size_t f = 0; f < bp.forms.size(); ++f)
+    if (bp.forms[f].form == EBTC_SPMV_PANELED) {
+      const Members m = members_of(bp, f);
+      bp.forms[f] = spmv_form(b, EBTC_SPMV_BALANCED, 0, 0, o->hub_threshold, bp.mixed() ? &m : nullptr);
+    }
+  return bp;
+}
+
+// The plan of a forward call. The tuner times launches over the whole batch. Under the plain schedule a launch covers
+// one realization: its tiles leave compute units idle and their preparation is launches of its own, so the
+// entry-balanced form runs instead (16 x ER n=1e5, degree 20: 34.1 ms paneled, 15.6 balanced; 2 x n=1e6: 7.7 and 6.6;
+// the other way round on Barabasi-Albert graphs, 8 x n=1e5: 16.6 and 32.8, which one cannot tell here).
+BatchPlan call_plan(const ebtc_batch* b, const ebtc_opts* o) {
+  return o->schedule == EBTC_SCHED_PLAIN ? balanced_plan(b, o) : spmv_plan(b, o);
 }
 
 LzArgs make_args(const ebtc_batch* b, const ebtc_opts* o, char* ws, const Layout& L) {
@@ -1167,7 +1182,10 @@ int ebtc_plan(ebtc_batch* b, const ebtc_opts* o, size_t* ws_bytes, size_t* ckpt_
   const BatchPlan bp = spmv_plan(b, o);
   rc = check_plan(b, bp);
   if (rc) return rc;
+  // one size for every schedule (call_plan)
   *ws_bytes = make_layout(b, o, bp).total;
+  const BatchPlan bal = balanced_plan(b, o);
+  if (bal.sig() != bp.sig()) *ws_bytes = std::max(*ws_bytes, make_layout(b, o, bal).total);
   if (ckpt_bytes) *ckpt_bytes = sizeof(double) * kCkptDoubles * (size_t)b->R;
   return EBTC_OK;
 }
@@ -1179,7 +1197,7 @@ int ebtc_scores(ebtc_batch* b, const ebtc_opts* o, void* ws, size_t ws_bytes, vo
   int rc = check_opts(o);
   if (rc) return rc;
   if (!ws || !scores_out || !log_scale_out) return fail(EBTC_EINVAL, "NULL workspace, scores or log_scale output");
-  const BatchPlan bp = spmv_plan(b, o);
+  const BatchPlan bp = call_plan(b, o);
   rc = check_plan(b, bp);
   if (rc) return rc;
   const Layout L = make_layout(b, o, bp);
@@ -1272,10 +1290,14 @@ int ebtc_scores_noalloc(ebtc_batch* b, const ebtc_opts* o, void* scores_out, dou
   int rc = check_opts(o);
   if (rc) return rc;
   if (!scores_out || !log_scale_out) return fail(EBTC_EINVAL, "NULL scores or log_scale output");
-  const BatchPlan bp = spmv_plan(b, o);
+  BatchPlan bp = call_plan(b, o);
   rc = check_plan(b, bp);
   if (rc) return rc;
-  const Layout L = make_layout(b, o, bp);
+  Layout L = make_layout(b, o, bp);
+  if (L.total > kScratchBytes) {
+    bp = balanced_plan(b, o);
+    L = make_layout(b, o, bp);
+  }
   if (L.total > kScratchBytes)
     return fail(EBTC_EWORKSPACE, "the batch needs a workspace of " + std::to_string(L.total) +
                                      " bytes; the static scratch holds " + std::to_string(kScratchBytes) +

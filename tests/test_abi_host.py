@@ -484,3 +484,24 @@ def test_generate_spec_layout():
     assert (f["p"], f["k"], f["beta"], f["seed"], f["first"], f["t"], f["targets"], f["pattern"]) == \
         (8, 16, 24, 32, 40, 48, 56, 64)
     assert ctypes.sizeof(A.GenSpec) == 72
+
+
+def test_plan_of_a_recorded_paneled_form_suits_every_schedule():
+    # the plain schedule runs the entry-balanced form there; a workspace planned under one schedule is taken under
+    # another, and the backward call, which always launches over the whole batch, plans one size
+    d, keep = make_desc(G=1, nreal=(4,), n=(30000,), nnz=(400000,) * 4)
+    rc, h = create(d)
+    assert rc == 0 and set_forms(h, [6])[0] == 0
+    sizes = [plan(h, m=30, schedule=s)[1] for s in (0, 1, 2)]
+    assert sizes[0] == sizes[1] == sizes[2]
+    assert sizes[0] >= plan(h, m=30, spmv=6)[1] and sizes[0] >= plan(h, m=30, spmv=5)[1]
+    back = []
+    for s in (0, 1, 2):
+        o, ws = A.Opts(), ctypes.c_size_t()
+        A.lib().ebtc_default_opts(ctypes.byref(o))
+        o.schedule = s
+        assert A.lib().ebtc_plan_backward(h, ctypes.byref(o), ctypes.byref(ws)) == A.EBTC_OK
+        back.append(ws.value)
+    assert back[0] == back[1] == back[2] > sizes[0]
+    assert plan(h, m=30, schedule=1, spmv=6)[1] == plan(h, m=30, spmv=6)[1]  # a named form stays
+    A.lib().ebtc_batch_destroy(h)

@@ -178,3 +178,26 @@ def test_breakdown_beside_long_rows_of_others(gpu_lib):
         ref = scored(b, spmv="stream", **kw)
         same = scored(b, spmv="paneled", **kw) == ref
         assert same, kw
+
+
+def test_recorded_form_in_the_fixed_array(gpu_lib):
+    # a recorded paneled form whose arenas pass the library's 64 MiB: the entry-balanced form, which fits, runs
+    from paper_1409_5000_amd import _abi as A
+    n = 60_000
+    rng = np.random.default_rng(37)
+    b = api().Batch.from_csr([[csr(n, G.er_keys(n, 36.0 / (n - 1), rng), rng, True) for _ in range(4)]], dtype="f32")
+    assert b.run(m=5, spmv="paneled").ws_bytes > A.NOALLOC_WS_BYTES > b.run(m=5, spmv="balanced").ws_bytes
+    b.set_forms(["paneled"])
+    import torch
+    for schedule in ("auto", "plain"):
+        out = b.scores_noalloc(m=5, schedule=schedule)
+        torch.cuda.synchronize()
+        same = (out.scores.cpu().numpy().tobytes(), out.log_scale.cpu().numpy().tobytes(),
+                out.diag_numpy().tobytes()) == scored(b, m=5, spmv="stream")
+        assert same, schedule
+    # a workspace planned under one schedule serves another
+    run = b.run(m=5, schedule="plain")
+    run.opts.schedule = api()._SCHED["batched"]
+    assert run.launch().scores.cpu().numpy().tobytes() == scored(b, m=5, spmv="stream")[0]
+    with pytest.raises(A.EbtcError):
+        b.scores_noalloc(m=5, spmv="paneled")  # by name: as asked
