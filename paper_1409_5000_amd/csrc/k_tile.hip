@@ -240,8 +240,9 @@ __global__ __launch_bounds__(kBlock) void k_tile_fill(LzArgs a, int t0, int coun
 // early second one, so that even the groups where classes meet seldom hold a row twice. Adds per group for 64 x
 // n=1e5, degree 20: 1.23 (first come, first placed: 1.90); n=4e5, degree 24: 1.17 (2.44).
 // Reads the columns twice and the values once, writes words and values: 20 bytes per weighted entry.
+// p0: the launch's first place.
 template <typename T, bool HAS_VAL>
-__global__ __launch_bounds__(kSortThreads) void k_tile_sort(LzArgs a) {
+__global__ __launch_bounds__(kSortThreads) void k_tile_sort(LzArgs a, int p0) {
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr int NT = kSortThreads, U = 8, K = kTileClasses;
   // the count's groups of 64 entries overlap by the K - 1 that decide their first entries' classes
@@ -252,7 +253,7 @@ __global__ __launch_bounds__(kSortThreads) void k_tile_sort(LzArgs a) {
   __shared__ int s_first[NT], s_len[NT];
   __shared__ int s_bad;
   // eight places, one per XCD, then their next bands
-  const int band = (blockIdx.x >> 3) % kTileBands, sh = (blockIdx.x >> 3) / kTileBands * 8 + (blockIdx.x & 7);
+  const int band = (blockIdx.x >> 3) % kTileBands, sh = p0 + (blockIdx.x >> 3) / kTileBands * 8 + (blockIdx.x & 7);
   const TileShare share = a.tile_share[sh];
   if (share.task < 0) return;
   const int tid = threadIdx.x, lane = tid & 63, w0r = tid - lane;  // w0r: the wave's first row slot
@@ -604,9 +605,9 @@ constexpr int kTileStream = 2;  // non-temporal: the matrix is read once per pro
 // 64 KB in flight per compute unit; measured at D U = 8, 16 and 18: 308, 226 and 209 us at n=1e5 x 64).
 // Short runs take short chunks: every chunk issues U loads, however few entries it holds (one graph of
 // n=1e6: 80 us with U = 2 against 103 with U = 6). All of a share's first loads wait on its record alone; the
-// step is opened from partials loaded with them and summed after the last panel.
+// step is opened from partials loaded with them and summed after the last panel. p0: the launch's first place.
 template <typename T, bool HAS_VAL, int U, int D>
-__global__ __launch_bounds__(kTileThreads) void k_spmv_tile(LzArgs a, int j) {
+__global__ __launch_bounds__(kTileThreads) void k_spmv_tile(LzArgs a, int j, int p0) {
   if (all_stopped(a, j)) return;
   constexpr int COLS = TileShape<T>::COLS, UL = TileShape<T>::UL, NT = kTileThreads;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -620,6 +621,7 @@ __global__ __launch_bounds__(kTileThreads) void k_spmv_tile(LzArgs a, int j) {
   static_assert(TileShape<T>::HCAP * sizeof(T) + NT / 64 * 8 + (kStreamRows + 1) * 4 <=
                     2 * COLS * sizeof(T) + sizeof(double) * kTileMaxRows, "scratch within the dynamic LDS");
   if (blockIdx.x < kTileHubGroups) {
+    if (p0 > 0) return;  // taken by the first of several launches
     for (int i = blockIdx.x; i < a.tile_count[2]; i += kTileHubGroups) {
       const HubBatch hb = a.hub_batch[i];
       const Task tk = a.tasks[hb.task];
@@ -629,7 +631,7 @@ __global__ __launch_bounds__(kTileThreads) void k_spmv_tile(LzArgs a, int j) {
     }
     return;
   }
-  const int sh = blockIdx.x - kTileHubGroups;
+  const int sh = p0 + blockIdx.x - kTileHubGroups;
   const TileShare share = a.tile_share[sh];
   const int task = uniform(share.task);
   if (task < 0) return;
@@ -836,6 +838,11 @@ hipError_t prepare_tile_t() {
   return e;
 }
 
+// Places of one launch: a launch's threads number less than 2^32, so batches of some 350000 realizations and more sort
+// in several launches, and those of two million multiply in several.
+constexpr int kSortPlaces = (int)(((int64_t)1 << 32) / (kTileBands * kSortThreads) / 8 * 8 - 8);
+constexpr int kTilePlaces = (int)((((int64_t)1 << 32) / kTileThreads - kTileHubGroups) / 8 * 8 - 8);
+
 template <typename T, bool HAS_VAL>
 hipError_t tile_prepare_t(const LzArgs& a, int t0, int count, hipStream_t s) {
   const int places = (a.ntile + 7) / 8 * 8;
@@ -845,8 +852,9 @@ hipError_t tile_prepare_t(const LzArgs& a, int t0, int count, hipStream_t s) {
   hipLaunchKernelGGL(k_tile_pack, dim3(1), dim3(1024), 0, s, a, t0, count, 1);
   hipLaunchKernelGGL(k_tile_fill, dim3((unsigned)((places + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, a, t0, count,
                      places);
-  hipLaunchKernelGGL((k_tile_sort<T, HAS_VAL>), dim3((unsigned)(places * kTileBands)), dim3(kSortThreads), sort_lds(a.pan_pmax),
-                     s, a);
+  for (int p0 = 0; p0 < places; p0 += kSortPlaces)
+    hipLaunchKernelGGL((k_tile_sort<T, HAS_VAL>), dim3((unsigned)(std::min(places - p0, kSortPlaces) * kTileBands)),
+                       dim3(kSortThreads), sort_lds(a.pan_pmax), s, a, p0);
   if constexpr (HAS_VAL) {
     if (a.first_in_prepare)
       hipLaunchKernelGGL((k_tile_hub_first<T>), dim3(kTileHubGroups), dim3(kTileThreads),
@@ -857,9 +865,11 @@ hipError_t tile_prepare_t(const LzArgs& a, int t0, int count, hipStream_t s) {
 
 template <typename T, bool HAS_VAL>
 hipError_t spmv_tile_t(int j, const LzArgs& a, hipStream_t s) {
-  const dim3 g((unsigned)((a.ntile + 7) / 8 * 8 + kTileHubGroups)), b(kTileThreads);
+  const int places = (a.ntile + 7) / 8 * 8;
   return tile_kernel<T, HAS_VAL>(a.tile_short, [&](auto k) {
-    hipLaunchKernelGGL(k, g, b, tile_lds<T>(), s, a, j);
+    for (int p0 = 0; p0 < places; p0 += kTilePlaces)
+      hipLaunchKernelGGL(k, dim3((unsigned)(std::min(places - p0, kTilePlaces) + kTileHubGroups)), dim3(kTileThreads),
+                         tile_lds<T>(), s, a, j, p0);
     return hipGetLastError();
   });
 }
@@ -881,7 +891,8 @@ int64_t tile_hub_rows(int64_t entries) { return entries / (kTileHubMin + 1) + 1;
 
 hipError_t launch_tile_prepare(int dtype, bool has_val, const LzArgs& a, int t0, int count, hipStream_t s) {
   if (a.pan_cols <= 0 || a.pan_cols > tile_max_cols(dtype) || a.pan_pmax < 1 || a.pan_pmax > kTileMaxPanels ||
-      a.tile_rows < 1 || a.tile_rows > kTileMaxRows || a.tile_least < 1 || a.tile_least > a.tile_rows || a.ntile < 1 || a.ntile > kTileMaxSlots || count < 1)
+      a.tile_rows < 1 || a.tile_rows > kTileMaxRows || a.tile_least < 1 || a.tile_least > a.tile_rows ||
+      a.ntile < 1 || a.ntile > kTileMaxSlots || count < 1)
     return hipErrorInvalidValue;
   if (dtype == EBTC_F64)
     return has_val ? tile_prepare_t<double, true>(a, t0, count, s) : tile_prepare_t<double, false>(a, t0, count, s);

@@ -201,3 +201,33 @@ def test_recorded_form_in_the_fixed_array(gpu_lib):
     assert run.launch().scores.cpu().numpy().tobytes() == scored(b, m=5, spmv="stream")[0]
     with pytest.raises(A.EbtcError):
         b.scores_noalloc(m=5, spmv="paneled")  # by name: as asked
+
+
+@pytest.mark.parametrize("n,R,weighted", [(40, 400_000, True), (6, 2_097_100, False)])
+def test_more_places_than_one_launch_takes(gpu_lib, n, R, weighted):
+    # two share slots a realization, twelve workgroups of 512 threads each in the sort (less than 2^32 threads a launch:
+    # 350000 realizations), one of 1024 in the product (2097020); paths of n nodes with a chord
+    import torch
+    A = np.diag(np.ones(n - 1), 1)
+    A[0, 2] = 1.0
+    A = A + A.T
+    rp = np.concatenate([[0], np.cumsum((A != 0).sum(1))]).astype(np.int32)
+    ci = np.nonzero(A)[1].astype(np.int32)
+    va = torch.linspace(0.5, 1.5, R * ci.size, dtype=torch.float32, device="cuda") if weighted else None
+    b = api().Batch([n], [R], np.arange(R) * (n + 1), np.arange(R + 1) * ci.size,
+                    torch.as_tensor(rp).cuda().repeat(R), torch.as_tensor(ci).cuda().repeat(R), va, "f32")
+    kw = dict(m=4, schedule="batched", hipgraph=False)
+    outs = []
+    for form in ("stream", "paneled"):
+        run = b.run(spmv=form, **kw)
+        run.ws.fill_(255)
+        out = run.launch()
+        torch.cuda.synchronize()
+        outs.append((out.scores.cpu().numpy().tobytes(), out.log_scale.cpu().numpy().tobytes(), out.diag_numpy().tobytes()))
+        del run, out
+    same = outs[0] == outs[1]
+    assert same
+    if weighted:  # the tuner tries the form on such a batch
+        api().tune_cache_clear()
+        assert "paneled" in b.tune(m=4)["ms_per_launch"]
+        api().tune_cache_clear()
