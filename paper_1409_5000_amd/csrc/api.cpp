@@ -788,8 +788,18 @@ bool wide_pays(const ebtc_batch* b, const ebtc_opts* o) {
   if (o->spmv == EBTC_SPMV_AUTO)
     for (const auto& f : b->tuned)
       if (f[0] == EBTC_SPMV_LANE_GROUPS || f[0] == EBTC_SPMV_LDS_STAGED) return false;
+  // A realization's entries per row at most. Denser graphs keep one workgroup's loads and long rows' chains busy past
+  // what the model below knows (gain over the per-phase schedule, smallest of 2100 to 9000 nodes, up to 700
+  // realizations: degree 64 pattern only 0.98, 80 0.90, 200 0.28; with values degree 32 1.02, 39 0.84).
+  constexpr int64_t kMostPattern = 64, kMostValues = 32;
+  const int64_t most = b->values ? kMostValues : kMostPattern;
+  int64_t r = 0;
+  for (int32_t g = 0; g < b->G; ++g)
+    for (int32_t k = 0; k < b->nreal[g]; ++k, ++r)
+      if (b->nnz_r[r] > most * b->n[g]) return false;
   // The two schedules' times by what bounds them, fitted to 700 calls on gfx950 (2100 to 9000 nodes, degree 2 to 25,
-  // 1 to 300 realizations, every dtype and option; it never chose the slower by more than 2%). A workgroup alone:
+  // 1 to 300 realizations, every dtype and option) and checked on 1200 more (to 14000 nodes, degree 64, 1500
+  // realizations, hub rows to 6200 entries); it never chose the slower by more than 2%. A workgroup alone:
   // a step's barriers and chains, the basis at 45 GB/s, its entries at 0.11 ns (more with values, and the more
   // workgroups share the L2); together no faster than the last-level cache, in rounds of 256. Per phase: 10 us per
   // step of an adaptive run up to its cap, 19 or 24 (FP64) of a fixed one, the basis, the entries at the rate of

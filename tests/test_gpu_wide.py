@@ -93,3 +93,19 @@ def test_many_rows_beyond_the_capacity(gpu_lib, dtype, n, cap):
                     torch.as_tensor(ci).cuda().repeat(R), None, dtype)
     check(b, m=8)
     check(b, m=0, tol=1e-8, m_max=40)
+
+
+@pytest.mark.parametrize("dtype,n,entries,R,weights", [("f64", 4000, 200, 300, False), ("f32", 4000, 39, 300, True)])
+def test_dense_graphs_stay_on_the_schedule_of_launches(gpu_lib, dtype, n, entries, R, weights):
+    # the workgroup's solve takes 3.4 and 1.2 times as long here
+    import torch
+    rng = np.random.default_rng(11)
+    ci = np.sort(rng.integers(0, n // entries, (n, entries)) + np.arange(entries) * (n // entries), axis=1)
+    z = n * entries
+    b = api().Batch([n], [R], np.arange(R) * (n + 1), np.arange(R + 1) * z,
+                    torch.arange(0, z + 1, entries, dtype=torch.int32, device="cuda").repeat(R),
+                    torch.as_tensor(ci.astype(np.int32).reshape(-1)).cuda().repeat(R),
+                    torch.full((R * z,), 0.5, device="cuda") if weights else None, dtype)
+    run = b.run(m=0)
+    run.launch()
+    assert run.profile()["solve"][1] == 0
