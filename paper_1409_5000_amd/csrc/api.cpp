@@ -1771,25 +1771,35 @@ size_t shared_layout(int32_t dtype, int32_t n, int32_t count, size_t off, char* 
   q->s = (double*)take(sizeof(double) * (size_t)count);
   q->cut = (int32_t*)take(sizeof(int32_t) * ((size_t)q->shares + 1));
   q->longs = (int32_t*)take(sizeof(int32_t) * (size_t)n);
-  q->seen = (int32_t*)take(3 * sizeof(int32_t));
+  q->seen = (SharedSeen*)take(sizeof(SharedSeen));
   return off;
 }
 
-// Together or process by process. A few long rows decide at once: the stream form holds up its launch for them
-// (n=300000 Barabasi-Albert, degree 24, two processes: 46.7 ms, together 5.0; where most rows are long, in a dense
-// matrix, no row does). Otherwise by the times per step, measured on gfx950: the stream form's gathers, at the rate
+// Together or process by process, by the times per step, measured on gfx950. The stream form: its gathers, at the rate
 // of a graph whose neighbours lie close together (500 G/s, FP64 470; a random graph's 185 and 205 are not known
-// beforehand), against a wavefront load per entry (12 cycles of a compute unit, FP64 23, or its bytes at 7.2 TB/s),
-// packing the vectors, and the launches; no less than the longest row takes (60 ns an entry, together 30). n=1e5, degree 20, FP32, random / ring lattice, together against one by one:
-// 8 processes 1.50 / 2.38 and 1.50 / 1.31 ms, 16 processes 1.72 / 4.20 and 1.73 / 2.06.
-bool shared_pays(int32_t dtype, int32_t n, int32_t count, int32_t rows, int32_t entries, int32_t longest) {
-  if (entries < 0 || entries > 0x7fffffff - 256) return false;  // the kernels look a few entries ahead
-  if (rows > 0) return rows <= n / 16;
+// beforehand), and where there are long chains of adds, what its slowest group of rows, or all of them on the whole
+// chip, take at 40 ns an entry of a chunk's longest row (n=300000 Barabasi-Albert, degree 24, two processes: 67236
+// entries, 2.73 ms a step, together 0.24; one row of 1100 in a ring lattice of n=1e6, FP64: 0.16 ms, together 0.45).
+// Together: packing the vectors, a wavefront load per entry (12 cycles of a compute unit, FP64 23, or its bytes at 7.2
+// TB/s) and the launches, beside the long rows' chains (34 ns an entry, FP32 with values 41) or before the chain of the
+// longest of the others, which a wavefront adds. Over 2400 calls on lattices, random and Barabasi-Albert graphs with 1
+// to 200 rows of 600 to 20000 entries it chose the slower by more than 3% twice, by 8% at most. In dense matrices, where
+// most rows are long, it is never taken.
+// n=1e5, degree 20, FP32, random / ring lattice, together against one by one: 8 processes 1.50 / 2.38 and 1.50 / 1.31 ms,
+// 16 processes 1.72 / 4.20 and 1.73 / 2.06.
+bool shared_pays(int32_t dtype, bool has_val, int32_t n, int32_t count, const SharedSeen& g) {
+  if (g.entries < 0 || g.entries > 0x7fffffff - 256) return false;  // the kernels look a few entries ahead
+  if (g.rows > n / 16) return false;
   const bool f64 = dtype == EBTC_F64;
-  const double es = f64 ? 8 : 4, bytes = (double)shared_stride_bytes(dtype, count), nnz = entries;
-  const double alone = std::max(nnz * count / (f64 ? 470e9 : 500e9), longest * 60e-9);
+  const double es = f64 ? 8 : 4, bytes = (double)shared_stride_bytes(dtype, count), nnz = g.entries;
+  const double wait = std::max(g.group * 40e-9, g.groups * 27e-12 * count);
+  const double alone = nnz * count / (f64 ? 470e9 : 500e9) + std::max(0.0, wait - 5e-6);
   const double entry = std::max((f64 ? 38e-12 : 19.5e-12) * ((count + 63) / 64), bytes / 7.2e12);
-  return alone > std::max(nnz * entry, longest * 30e-9) + n * (count * es + bytes) / 2.6e12 + 10e-6;
+  const double loads = (nnz - g.longs) * entry, add = has_val && !f64 ? 41e-9 : 34e-9;
+  const double wave = has_val ? (f64 ? 35e-9 : 28e-9) : 18e-9;
+  const double rows = g.rows > 0 ? std::max({std::max(loads, g.big * 40e-9) + 10e-6, g.row * add, g.longs * add * 1e-3 * count})
+                                 : loads + std::max(10e-6, 5e-6 + g.row * wave);
+  return alone > n * (count * es + bytes) / 2.6e12 + rows;
 }
 }  // namespace
 
@@ -1828,20 +1838,20 @@ int ebtc_subgraph_centrality(int32_t dtype, int32_t n, const int32_t* row_ptr, c
   hipStream_t s = (hipStream_t)stream;
   char* w = (char*)ws;
   // first, so that it runs beside the host's copies of the tables
-  if (q.count) EBTC_LAUNCH(launch_shared_prepare(row_ptr, q, n, s));
+  if (q.count) EBTC_LAUNCH(launch_shared_prepare(dtype, row_ptr, q, n, s));
   rc = upload_tables(&b, w, L, bp, s);
   if (rc) return rc;
   LzArgs a = make_args(&b, &o, w, L);
   const std::vector<FArgs> fa = form_args(&b, a, w, L, bp);
-  int32_t seen[3] = {0, 0, 0};
+  SharedSeen seen{};
   if (q.count) {
     q.wstep = b.tasks[1].w_off - b.tasks[0].w_off;
-    EBTC_HIP(hipMemcpyAsync(seen, q.seen, sizeof(seen), hipMemcpyDeviceToHost, s));
+    EBTC_HIP(hipMemcpyAsync(&seen, q.seen, sizeof(seen), hipMemcpyDeviceToHost, s));
   }
   // the task table lives on this call's stack: wait until the copy has read it
   EBTC_HIP(hipStreamSynchronize(s));
-  if (q.count && !shared_pays(dtype, n, count, seen[0], seen[1], seen[2])) q.count = 0;
-  q.rows = seen[0];
+  if (q.count && !shared_pays(dtype, values != nullptr, n, count, seen)) q.count = 0;
+  q.rows = seen.rows;
   EBTC_LAUNCH(launch_blkmap(a.tasks, b.R, (int32_t*)(w + L.off_blkmap), s));
   EBTC_LAUNCH(launch_start_unit(dtype, a, nodes, L.total_blocks, s));
   rc = run_steps(&b, &o, a, fa, L.total_blocks, 0, b.R, s, nullptr, false, q.count ? &q : nullptr);

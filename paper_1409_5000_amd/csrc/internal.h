@@ -227,6 +227,18 @@ hipError_t launch_row_max(const Task* tasks, const int32_t* row_ptr, int64_t R, 
 hipError_t launch_start(int dtype, const LzArgs& a, int64_t nblocks, hipStream_t s);
 // Subgraph centrality: processes started at e_{nodes[r]}, and SC = e^{theta} y_0 per process.
 // Products of processes that share one matrix (k_shared.hip).
+// What the preparation finds of the rows. Costs are those of the stream form, in entries of a row's chain of adds: a
+// group of 256 rows takes its rows in chunks of the form's capacity, each as long as its longest row; a row beyond
+// the capacity is shared out, a sixteenth.
+struct SharedSeen {
+  int32_t rows;     // long rows (kSharedLong)
+  int32_t entries;
+  int32_t row;      // longest row of at most the capacity
+  int32_t big;      // of the longest row beyond it
+  int32_t group;    // most of a group
+  int32_t groups;   // sum over the groups with a row above 256 entries
+  int32_t longs;    // sum over the long rows
+};
 struct SharedMat {
   int32_t count;    // processes
   int32_t shares;   // wavefronts' row shares
@@ -235,13 +247,13 @@ struct SharedMat {
   double* s;        // [count] scales of the step; kSharedStopped: the process takes no part
   int32_t* cut;     // [shares + 1] first rows
   int32_t* longs;   // [n] long rows
-  int32_t* seen;    // [3] long rows, entries, entries of the longest row
+  SharedSeen* seen;
   int32_t rows;     // long rows, known to the host once the preparation has run
 };
 constexpr double kSharedStopped = -1.0;
 size_t shared_stride_bytes(int dtype, int32_t count);  // bytes of x per node
 int32_t shared_shares(int dtype, int32_t n);
-hipError_t launch_shared_prepare(const int32_t* row_ptr, const SharedMat& q, int32_t n, hipStream_t s);
+hipError_t launch_shared_prepare(int dtype, const int32_t* row_ptr, const SharedMat& q, int32_t n, hipStream_t s);
 hipError_t launch_shared_step(int dtype, bool has_val, int j, const LzArgs& a, const SharedMat& q, int32_t n,
                               hipStream_t s);
 hipError_t launch_start_unit(int dtype, const LzArgs& a, const int32_t* nodes, int64_t nblocks, hipStream_t s);

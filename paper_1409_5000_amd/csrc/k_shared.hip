@@ -33,11 +33,7 @@ __device__ inline int shared_stride(int cnt) {  // whole 64-byte pieces
 __global__ __launch_bounds__(kBlock) void k_shared_cut(int32_t n, const int32_t* rp, SharedMat q) {
   const int s = blockIdx.x * kBlock + threadIdx.x;
   if (s > q.shares) {
-    if (s == q.shares + 1) {
-      q.seen[0] = 0;
-      q.seen[1] = rp[n] - rp[0];
-      q.seen[2] = 0;
-    }
+    if (s == q.shares + 1) *q.seen = {0, rp[n] - rp[0], 0, 0, 0, 0, 0};
     return;
   }
   const int32_t z = rp[0];
@@ -50,17 +46,50 @@ __global__ __launch_bounds__(kBlock) void k_shared_cut(int32_t n, const int32_t*
   q.cut[s] = s == q.shares ? n : lo;
 }
 
-// The long rows, in any order (each is a result of its own), and the longest.
-__global__ __launch_bounds__(kBlock) void k_shared_long(int32_t n, const int32_t* rp, SharedMat q) {
+// The long rows, in any order (each is a result of its own), and the rest of SharedSeen: a workgroup per group of rows
+// of the stream form, whose walk one thread repeats where there are rows to wait for. cap: that form's capacity.
+__global__ __launch_bounds__(kBlock) void k_shared_long(int32_t n, const int32_t* rp, SharedMat q, int cap) {
+  static_assert(kBlock == kStreamRows, "a thread per row of a group");
   const int r = blockIdx.x * kBlock + threadIdx.x;
+  SharedSeen* seen = q.seen;
   int len = r < n ? rp[r + 1] - rp[r] : 0;
-  if (len > kSharedLong) q.longs[atomicAdd(q.seen, 1)] = r;
-  __shared__ int top;
-  if (threadIdx.x == 0) top = 0;
+  if (len > kSharedLong) {
+    q.longs[atomicAdd(&seen->rows, 1)] = r;
+    atomicAdd(&seen->longs, len > cap ? len / 16 : len);
+    if (len > cap) atomicMax(&seen->big, len / 16);
+  }
+  __shared__ int top, most, lens[kBlock];
+  if (threadIdx.x == 0) top = most = 0;
+  lens[threadIdx.x] = len;
   __syncthreads();
   atomicMax(&top, len);
+  if (len <= cap) atomicMax(&most, len);
   __syncthreads();
-  if (threadIdx.x == 0) atomicMax(q.seen + 2, top);
+  if (threadIdx.x != 0) return;
+  // most groups have nothing larger to say, and thousands of atomics on one word take longer than the rest
+  auto raise = [](int32_t* x, int v) {
+    if (__hip_atomic_load(x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < v) atomicMax(x, v);
+  };
+  raise(&seen->row, most);
+  int cost = top;
+  if (top > 256) {
+    int held = 0, longest = 0;  // of the chunk
+    cost = 0;
+    for (int i = 0; i < kBlock; ++i) {
+      const int l = lens[i];
+      if (l > cap || held + l > cap) {
+        cost += longest + (l > cap ? l / 16 : 0);
+        held = longest = 0;
+      }
+      if (l <= cap) {
+        held += l;
+        longest = max(longest, l);
+      }
+    }
+    cost += longest;
+    atomicAdd(&seen->groups, cost);
+  }
+  raise(&seen->group, cost);
 }
 
 // Node-major copy of the processes' current vectors, and their scales: workgroups [0, count) close the last step
@@ -270,13 +299,13 @@ size_t shared_stride_bytes(int dtype, int32_t count) {
   return es * full + (rem * es + 63) / 64 * 64;
 }
 
-hipError_t launch_shared_prepare(const int32_t* row_ptr, const SharedMat& q, int32_t n, hipStream_t s) {
+hipError_t launch_shared_prepare(int dtype, const int32_t* row_ptr, const SharedMat& q, int32_t n, hipStream_t s) {
   hipLaunchKernelGGL(k_shared_cut, dim3((unsigned)((q.shares + 2 + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, n,
                      row_ptr, q);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_shared_long, dim3((unsigned)(((int64_t)n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, n,
-                     row_ptr, q);
+                     row_ptr, q, dtype == EBTC_F64 ? StreamShape<double>::CAP : StreamShape<float>::CAP);
   return hipGetLastError();
 }
 

@@ -77,3 +77,20 @@ def test_a_workspace_for_the_processes_alone_is_taken(gpu_lib):
         torch.cuda.synchronize()
         got.append(out.cpu().numpy().tobytes())
     assert got[0] == got[1]
+
+
+# Whether one isolated long row makes the products formed together the path is a matter of times. A group of 256 rows that
+# the stream form walks in several chunks does: the edges of CASES with eight to twelve long rows side by side.
+GROUPS = [
+    (4096, 1025, 12, (), 2), (4097, 1025, 12, (3000, 3001), 16), (4159, 1100, 12, (3000,), 17), (4160, 1100, 12, (), 33),
+    (5000, 1025, 12, tuple(range(1900, 2100)), 64), (4999, 1025, 12, (4998,), 65), (4099, 4000, 8, (), 130),
+    (20000, 6144, 9, (300,), 50), (20000, 3073, 9, (), 3), (140000, 2000, 12, (), 9),
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("weights", [False, True])
+@pytest.mark.parametrize("n,length,rows,empty,count", GROUPS)
+def test_long_rows_side_by_side(gpu_lib, n, length, rows, empty, count, weights, dtype):
+    hubs = tuple((256 + i, length + i % 2) for i in range(rows))
+    test_together_equals_one_by_one(None, n, hubs, empty, count, weights, dtype)
