@@ -33,8 +33,7 @@ __device__ inline bool step_skipped(const LzArgs& a, const RState* st, int j) {
 // record a stop while the others start: a stop found by this launch does not count, so that all threads of a workgroup
 // see the same (barriers follow); the closing, which every workgroup does for itself, then ends them.
 __device__ inline bool product_skipped(const LzArgs& a, const RState* st, int j) {
-  const int d = st->done;
-  return (d != 0 && d != 2 + j) || (a.stop_mused && j + 1 >= st->m_used);
+  return (unsigned)(st->done - 1) < (unsigned)(j + 1) || (a.stop_mused && j + 1 >= st->m_used);  // 1 or 2 + i, i < j
 }
 
 // True when every realization of the launch stopped at step j - 1's adaptive check: the launch's
