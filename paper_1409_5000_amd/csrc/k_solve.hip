@@ -28,7 +28,10 @@ namespace ebtc {
 namespace {
 
 constexpr int kSolveCap = kRowsPerBlock;  // product slots: every row of a simple graph on <= 2048 nodes fits
-constexpr int kSolveOcc = 4;  // wavefronts per SIMD
+// Wavefronts per SIMD, workgroups per compute unit. FP32 without the entries in LDS two, for whose registers more of the
+// product's loads are in flight (n=1500, degree 60, m=20: 4.42 to 3.94 ms; FP64 would lose 7%).
+constexpr int solve_occ(bool csr_lds, size_t es) { return csr_lds || es == 8 ? 4 : 2; }
+constexpr int kSolveUnits = 256;  // compute units
 constexpr int kSolveRed = (kDotsThreads / 64) * 16;
 
 // Dynamic LDS of one launch (byte offsets, host-computed from the largest realization).
@@ -264,7 +267,7 @@ __device__ inline Task uniform_task(const Task& t) {
 }
 
 template <typename T, bool HAS_VAL, bool CSR_LDS, bool V_LDS>
-__global__ __launch_bounds__(kBlock, kSolveOcc) void k_solve_1(LzArgs a, SolveLds L, int steps, int shift, double tol,
+__global__ __launch_bounds__(kBlock, solve_occ(CSR_LDS, sizeof(T))) void k_solve_1(LzArgs a, SolveLds L, int steps, int shift, double tol,
                                                     ebtc_diag* diag, double* ckpt) {
   extern __shared__ __align__(16) unsigned char dyn[];
   __shared__ T prod[CSR_LDS ? 1 : kSolveCap];
@@ -410,19 +413,27 @@ size_t solve_static_bytes(hipError_t* err) {
 
 // The largest static LDS of the instantiations that a launch chooses from.
 template <typename T, bool HAS_VAL>
-hipError_t prepare_solve_t(size_t* bytes = nullptr) {
+hipError_t prepare_solve_t(size_t* bytes = nullptr, size_t* csr = nullptr) {
   hipError_t e = hipSuccess;
   const size_t b = std::max(std::max(solve_static_bytes<T, HAS_VAL, true, true>(&e), solve_static_bytes<T, HAS_VAL, true, false>(&e)),
                             std::max(solve_static_bytes<T, HAS_VAL, false, true>(&e), solve_static_bytes<T, HAS_VAL, false, false>(&e)));
   if (bytes) *bytes = b;
+  if (csr) *csr = solve_static_bytes<T, HAS_VAL, true, true>(&e);
   return e;
 }
 
 size_t align16(size_t x) { return (x + 15) / 16 * 16; }
 
-// LDS plan of a launch: v_j, w and the row pointers always; then the basis, then the CSR entries,
-// each where it still fits next to what is placed.
-SolveLds solve_lds(size_t es, bool has_val, int n_max, int64_t z_max, int steps, size_t budget) {
+// LDS plan of a launch: v_j, w and the row pointers always, then the CSR entries where they fit, then the basis where it
+// fits beside them (or, without them, alone). The entries come first: read from memory the product walks them chunk by
+// chunk with barriers (300 x n=700, degree 20, FP64, m=20: 1.03 ms with the basis in LDS, 0.41 with the entries). The
+// basis stays in the workspace, too, where a compute unit then holds so many more workgroups that the launch takes fewer
+// rounds (1500 x n=1200, degree 3, FP64, m=10: 0.93 ms with the basis in LDS, 0.56 without; 300 x n=1500, degree 60, FP32,
+// m=20, no entries in LDS: 9.67 and 4.71; in one round either way, 300 of n=300: 0.20 and 0.22). fixed, fixed_csr: static
+// LDS at most, and with the entries in LDS.
+SolveLds solve_lds(size_t es, bool has_val, int n_max, int64_t z_max, int steps, int64_t count, size_t fixed,
+                   size_t fixed_csr) {
+  const size_t budget = kLdsBytes - fixed;
   SolveLds L{};
   size_t off = 0;
   L.x_off = (int32_t)off;
@@ -432,20 +443,29 @@ SolveLds solve_lds(size_t es, bool has_val, int n_max, int64_t z_max, int steps,
   L.rp_off = (int32_t)off;
   off = align16(off + (size_t)(n_max + 1) * 4);
   const size_t vb = (size_t)(steps + 1) * n_max * es;
-  L.v_off = -1;
-  if (off + vb <= budget) {
-    L.v_off = (int32_t)off;
-    off = align16(off + vb);
-  }
   const size_t cb = align16((size_t)z_max * 2) + (has_val ? (size_t)z_max * es : 0);
-  L.c_off = L.val_off = -1;
-  if (off + cb <= budget) {
+  L.v_off = L.c_off = L.val_off = -1;
+  const bool csr = off + cb <= budget;
+  const size_t rest = csr ? align16(off + cb) : off;  // beside the basis
+  const auto held = [&](size_t bytes) {  // workgroups of a compute unit
+    return std::min<int64_t>(solve_occ(csr, es), kLdsBytes / (bytes + (csr ? fixed_csr : fixed)));
+  };
+  const auto rounds = [&](size_t bytes) {
+    const int64_t once = kSolveUnits * held(bytes);
+    return (count + once - 1) / once;
+  };
+  const bool basis = rest + vb <= budget && rounds(rest + vb) <= rounds(rest);
+  if (csr) {
     L.c_off = (int32_t)off;
     off = align16(off + (size_t)z_max * 2);
     if (has_val) {
       L.val_off = (int32_t)off;
       off = align16(off + (size_t)z_max * es);
     }
+  }
+  if (basis) {
+    L.v_off = (int32_t)off;
+    off = align16(off + vb);
   }
   L.z_max = (int32_t)std::min<int64_t>(z_max, INT32_MAX);
   L.bytes = (int32_t)off;
@@ -455,10 +475,10 @@ SolveLds solve_lds(size_t es, bool has_val, int n_max, int64_t z_max, int steps,
 template <typename T, bool HAS_VAL>
 hipError_t solve_t(const LzArgs& a, int64_t count, int steps, int shift, double tol, ebtc_diag* diag, double* ckpt,
                    int n_max, int64_t z_max, hipStream_t s) {
-  size_t fixed = 0;
-  const hipError_t e = prepare_solve_t<T, HAS_VAL>(&fixed);
+  size_t fixed = 0, fixed_csr = 0;
+  const hipError_t e = prepare_solve_t<T, HAS_VAL>(&fixed, &fixed_csr);
   if (e != hipSuccess) return e;
-  const SolveLds L = solve_lds(sizeof(T), HAS_VAL, n_max, z_max, steps, kLdsBytes - fixed);
+  const SolveLds L = solve_lds(sizeof(T), HAS_VAL, n_max, z_max, steps, count, fixed, fixed_csr);
   auto* solve = L.v_off >= 0 ? (L.c_off >= 0 ? k_solve_1<T, HAS_VAL, true, true> : k_solve_1<T, HAS_VAL, false, true>)
                              : (L.c_off >= 0 ? k_solve_1<T, HAS_VAL, true, false> : k_solve_1<T, HAS_VAL, false, false>);
   hipLaunchKernelGGL(solve, dim3((unsigned)count), dim3(kBlock), (size_t)L.bytes, s, a, L, steps, shift, tol, diag, ckpt);

@@ -168,3 +168,26 @@ def test_single_schedule_refuses_what_it_cannot_run(gpu_lib):
         with pytest.raises(Exception):
             small.scores(m=10, schedule="single", **kw)
         small.scores(m=10, schedule="auto", **kw)  # auto falls back to the per-phase schedule
+
+
+@pytest.mark.parametrize("valued", [False, True])
+@pytest.mark.parametrize("dtype,n,degree,m,R", [
+    # entries and basis in LDS; the entries alone, too large beside the basis; the basis alone; neither; one round of
+    # workgroups and more than two (the basis then stays in the workspace where it halves their number)
+    ("f64", 300, 20, 20, 40), ("f64", 700, 20, 20, 40), ("f32", 1500, 12, 20, 40), ("f64", 600, 200, 20, 40),
+    ("f32", 1500, 100, 20, 300), ("f64", 2048, 60, 40, 20), ("f64", 1200, 3, 10, 600), ("f32", 400, 12, 40, 2100)])
+def test_what_a_launch_holds_in_lds(gpu_lib, dtype, n, degree, m, R, valued):
+    import torch
+    rng = np.random.default_rng(n + degree)
+    A = rng.random((n, n)) < degree / (n - 1)
+    A = np.triu(A, 1)
+    A = A | A.T
+    rp = np.concatenate([[0], np.cumsum(A.sum(1))]).astype(np.int32)
+    ci = np.nonzero(A)[1].astype(np.int32)
+    va = None
+    if valued:
+        va = torch.as_tensor(0.5 + ((np.nonzero(A)[0] + ci) % 7) / 7.0, device="cuda",
+                             dtype=torch.float64 if dtype == "f64" else torch.float32).repeat(R)
+    b = api().Batch([n], [R], np.arange(R) * (n + 1), np.arange(R + 1) * ci.size,
+                    torch.as_tensor(rp).cuda().repeat(R), torch.as_tensor(ci).cuda().repeat(R), va, dtype)
+    assert_same(outputs(b, m=m, schedule="single"), outputs(b, m=m, schedule="batched", hipgraph=False))
