@@ -191,3 +191,18 @@ def test_what_a_launch_holds_in_lds(gpu_lib, dtype, n, degree, m, R, valued):
     b = api().Batch([n], [R], np.arange(R) * (n + 1), np.arange(R + 1) * ci.size,
                     torch.as_tensor(rp).cuda().repeat(R), torch.as_tensor(ci).cuda().repeat(R), va, dtype)
     assert_same(outputs(b, m=m, schedule="single"), outputs(b, m=m, schedule="batched", hipgraph=False))
+
+
+@pytest.mark.parametrize("dtype,valued", [("f64", False), ("f64", True), ("f32", True), ("f32", False)])
+def test_rows_of_every_length(gpu_lib, dtype, valued):
+    # rows of 0 to 70 entries, one of all nodes, values of both signs, zeros among them: eight entries at a time with and
+    # without a remainder, whose places past the row must not change a sum
+    rng = np.random.default_rng(41)
+    n = 900
+    lengths = np.concatenate([np.arange(71), rng.integers(0, 40, n - 72), [n]])
+    rp = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    ci = np.concatenate([np.sort(rng.choice(n, k, replace=False)) for k in lengths]).astype(np.int32)
+    va = rng.choice([-1.0, -0.0, 0.0, 0.25, 3.0, 1e-30], ci.size) if valued else None
+    b = api().Batch.from_csr([[(rp, ci, va)] * 3 if valued else [(rp, ci)] * 3], dtype=dtype)
+    for kw in (dict(m=6), dict(m=0, tol=1e-8, m_max=20)):
+        assert_same(outputs(b, schedule="single", **kw), outputs(b, schedule="batched", hipgraph=False, **kw))
