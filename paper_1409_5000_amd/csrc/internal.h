@@ -317,6 +317,8 @@ hipError_t prepare_tile_kernels();
 // The shares and the sorted entries of realizations [t0, t0 + count).
 hipError_t launch_tile_prepare(int dtype, bool has_val, const LzArgs& a, int t0, int count, hipStream_t s);
 hipError_t launch_spmv_tile(int dtype, bool has_val, int j, const LzArgs& a, hipStream_t s);
+// Step 0's product from the all-ones start once more, as the preparation of a weighted graph wrote it.
+hipError_t launch_tile_first(int dtype, const LzArgs& a, hipStream_t s);
 
 // ---- launchers (k_tridiag.hip)
 // mode 0: final (closes step m_steps-1 when still open; writes y/theta/est, diag, checkpoint);

@@ -843,6 +843,13 @@ hipError_t prepare_tile_t() {
 constexpr int kSortPlaces = (int)(((int64_t)1 << 32) / (kTileBands * kSortThreads) / 8 * 8 - 8);
 constexpr int kTilePlaces = (int)((((int64_t)1 << 32) / kTileThreads - kTileHubGroups) / 8 * 8 - 8);
 
+template <typename T>
+hipError_t hub_first_t(const LzArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL((k_tile_hub_first<T>), dim3(kTileHubGroups), dim3(kTileThreads), TileShape<T>::HCAP * sizeof(T), s,
+                     a);
+  return hipGetLastError();
+}
+
 template <typename T, bool HAS_VAL>
 hipError_t tile_prepare_t(const LzArgs& a, int t0, int count, hipStream_t s) {
   const int places = (a.ntile + 7) / 8 * 8;
@@ -855,11 +862,8 @@ hipError_t tile_prepare_t(const LzArgs& a, int t0, int count, hipStream_t s) {
   for (int p0 = 0; p0 < places; p0 += kSortPlaces)
     hipLaunchKernelGGL((k_tile_sort<T, HAS_VAL>), dim3((unsigned)(std::min(places - p0, kSortPlaces) * kTileBands)),
                        dim3(kSortThreads), sort_lds(a.pan_pmax), s, a, p0);
-  if constexpr (HAS_VAL) {
-    if (a.first_in_prepare)
-      hipLaunchKernelGGL((k_tile_hub_first<T>), dim3(kTileHubGroups), dim3(kTileThreads),
-                         TileShape<T>::HCAP * sizeof(T), s, a);
-  }
+  if constexpr (HAS_VAL)
+    if (a.first_in_prepare) return hub_first_t<T>(a, s);
   return hipGetLastError();
 }
 
@@ -897,6 +901,14 @@ hipError_t launch_tile_prepare(int dtype, bool has_val, const LzArgs& a, int t0,
   if (dtype == EBTC_F64)
     return has_val ? tile_prepare_t<double, true>(a, t0, count, s) : tile_prepare_t<double, false>(a, t0, count, s);
   return has_val ? tile_prepare_t<float, true>(a, t0, count, s) : tile_prepare_t<float, false>(a, t0, count, s);
+}
+
+// The product with the ones gives every row's values in entry order, as the sort sums them, but for rows beyond the
+// stream form's capacity, which k_tile_hub_first writes again with the other long rows.
+hipError_t launch_tile_first(int dtype, const LzArgs& a, hipStream_t s) {
+  const hipError_t e = launch_spmv_tile(dtype, true, 0, a, s);
+  if (e != hipSuccess) return e;
+  return dtype == EBTC_F64 ? hub_first_t<double>(a, s) : hub_first_t<float>(a, s);
 }
 
 hipError_t launch_spmv_tile(int dtype, bool has_val, int j, const LzArgs& a, hipStream_t s) {

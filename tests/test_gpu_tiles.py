@@ -231,3 +231,26 @@ def test_more_places_than_one_launch_takes(gpu_lib, n, R, weighted):
         api().tune_cache_clear()
         assert "paneled" in b.tune(m=4)["ms_per_launch"]
         api().tune_cache_clear()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_second_pass_of_the_memory_bounded_form(gpu_lib, dtype):
+    # step 0 of the second pass comes from the sorted entries: long rows on both sides of the stream form's capacity
+    # (whose first product is in entry order, the others not), of a batch of products, and columns out of order
+    n = 50_000
+    rng = np.random.default_rng(43)
+    rows = [(5, 257), (6, 300), (70, 1030), (9000, 3071), (9001, 3100), (9002, 6140), (9003, 6200), (30000, 16400),
+            (30001, 33000)] + [(20000 + i, 260 + 9 * i) for i in range(70)]
+    rp, ci, va = csr(n, hubs(n, rows, rng), rng, True)
+    b = api().Batch.from_csr([[(rp, ci, va), csr(n, hubs(n, rows[:3], rng), rng, True)]], dtype=dtype)
+    k = int(rp[40_000])
+    assert rp[40_001] - k >= 2
+    ci2, va2 = ci.copy(), va.copy()
+    ci2[[k, k + 1]], va2[[k, k + 1]] = ci[[k + 1, k]], va[[k + 1, k]]
+    c = api().Batch.from_csr([[(rp, ci2, va2)]], dtype=dtype)
+    for batch in (b, c):
+        for kw in (dict(m=8, reorth=0), dict(m=0, tol=1e-6, m_max=30, reorth=0),
+                   dict(m=8, reorth=0, schedule="plain")):
+            ref = scored(batch, spmv="stream", **kw)
+            same = scored(batch, spmv="paneled", **kw) == ref
+            assert same, kw
