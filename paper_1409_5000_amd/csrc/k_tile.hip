@@ -53,9 +53,13 @@ struct TileShape {
   static constexpr int UL = COLS * (int)sizeof(T) / 16 / (kTileLoaders * 64);  // 16-byte loads per loader lane
 };
 
-// Rows with more entries are summed apart: those of kTileHubMin entries and six times the realization's mean.
+// Rows with more entries are summed apart: than kTileHubMin and six times the realization's mean, or than the stream
+// form's capacity, beyond which that form's sums are not in entry order.
 constexpr int kTileHubMin = 256;
-__device__ inline int tile_hub(int64_t n, int64_t z) { return (int)max((int64_t)kTileHubMin, min((int64_t)1 << 30, 6 * z / max(n, (int64_t)1))); }
+template <typename T>
+__device__ inline int tile_hub(int64_t n, int64_t z) {
+  return (int)max((int64_t)kTileHubMin, min((int64_t)StreamShape<T>::CAP, 6 * z / max(n, (int64_t)1)));
+}
 
 // word of an entry: column in the panel << 2 (13 bits), row in the band << 16 (10 bits), rank << 26
 __device__ inline uint32_t tile_word(int col, int row, int rank) {
@@ -267,7 +271,7 @@ __global__ __launch_bounds__(kSortThreads) void k_tile_sort(LzArgs a, int p0) {
   const int32_t* rp = a.row_ptr + tk.rowptr_off;
   const int32_t* ci = a.col_idx + tk.nnz_off;
   const T* va = HAS_VAL ? (const T*)a.values + tk.nnz_off : nullptr;
-  const int e0 = rp[rb], e1 = rp[re], blen = e1 - e0, hub = tile_hub(n, rp[n]);
+  const int e0 = rp[rb], e1 = rp[re], blen = e1 - e0, hub = tile_hub<T>(n, rp[n]);
   uint32_t* ent = a.tile_ent + tk.aux_off + e0;
   T* val = HAS_VAL ? (T*)a.tile_val + tk.aux_off + e0 : nullptr;
   const unsigned long long below = (1ull << lane) - 1ull;
@@ -798,7 +802,7 @@ __global__ __launch_bounds__(kTileThreads) void k_spmv_tile(LzArgs a, int j, int
   if (!open(&sj)) return;
   if (flag & kTileFlagHubs) {  // the long rows are written by their own workgroups
     const int32_t* rp0 = a.row_ptr + uniform(share.rowptr_off);
-    const int hub = tile_hub(n, rp0[n]);
+    const int hub = tile_hub<T>(n, rp0[n]);
     for (int i = tid; i < rows; i += NT)
       if (rp[i + 1] - rp[i] <= hub) w[i] = (T)(acc[i] * sj);
   } else {

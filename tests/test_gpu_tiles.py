@@ -254,3 +254,20 @@ def test_second_pass_of_the_memory_bounded_form(gpu_lib, dtype):
             ref = scored(batch, spmv="stream", **kw)
             same = scored(batch, spmv="paneled", **kw) == ref
             assert same, kw
+
+
+@pytest.mark.parametrize("dtype,degree,long_row", [("f64", 620, 3500), ("f32", 1200, 6500)])
+def test_rows_beyond_the_capacity_of_a_dense_graph(gpu_lib, dtype, degree, long_row):
+    # six times the mean passes the stream form's capacity here: rows between the two are long rows all the same (the
+    # stream form sums them in another order)
+    n = 8000
+    rng = np.random.default_rng(47)
+    lengths = rng.integers(degree - 100, degree + 100, n)
+    lengths[[3, 100, 101, 5000, 7999]] = long_row + np.array([0, 1, 2, 400, 64])
+    rp = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    ci = np.concatenate([np.sort(rng.choice(n, k, replace=False)) for k in lengths]).astype(np.int32)
+    b = api().Batch.from_csr([[(rp, ci, 0.5 + rng.random(ci.size))] * 2], dtype=dtype)
+    for kw in (dict(m=6), dict(m=6, reorth=0)):
+        ref = scored(b, spmv="stream", **kw)
+        same = scored(b, spmv="paneled", **kw) == ref
+        assert same, kw
