@@ -917,10 +917,10 @@ int run_pass2(const ebtc_batch* b, const ebtc_opts* o, const LzArgs& a1, const s
     if (j + 1 == steps) break;  // the last vector needed is v_{steps-1}
     for (const FArgs& x : fa) {
       if (x.nb == 0) continue;
-      // the second pass never skips step 0: the sort's product of the first pass is gone. The paneled form's sorted
-      // entries give it again (n=1e6 Barabasi-Albert, degree 16, FP64: the row sums from the CSR take 7.8 ms, 0.34 here)
-      if (j == 0 && x.sp.form == EBTC_SPMV_PANELED && x.a.first_in_prepare) {
-        EBTC_PHASE(prof, EBTC_PHASE_FIRST, launch_tile_first(b->dtype, x.a, s));
+      // the second pass never skips step 0: the sort's product of the first pass is gone
+      if (j == 0 && x.sp.form == EBTC_SPMV_PANELED && x.a.first_in_prepare) {  // the long rows as the sort does them
+        EBTC_PHASE(prof, EBTC_PHASE_FIRST, launch_first_short(b->dtype, x.a, x.nb, s));
+        EBTC_PHASE(prof, EBTC_PHASE_FIRST, launch_tile_hub_first(b->dtype, x.a, s));
         continue;
       }
       LzArgs xa = x.a;

@@ -261,6 +261,8 @@ hipError_t launch_sc_out(const RState* state, const Task* tasks, const int32_t* 
                          hipStream_t s);
 // Phase A: the SpMV kernel (column-segmented when a.seg_cols > 0, LDS-staged when a.seglen > 0, else
 // the CSR stream for lanes == 0 and lane groups otherwise).
+// Step 0's product of a weighted graph but for the paneled form's long rows.
+hipError_t launch_first_short(int dtype, const LzArgs& a, int64_t nblocks, hipStream_t s);
 hipError_t launch_spmv_step(int dtype, bool has_val, int lanes, int j, const LzArgs& a, int64_t nblocks,
                             hipStream_t s);
 hipError_t launch_dots_step(int dtype, int j, const LzArgs& a, int64_t nblocks, hipStream_t s);
@@ -317,8 +319,8 @@ hipError_t prepare_tile_kernels();
 // The shares and the sorted entries of realizations [t0, t0 + count).
 hipError_t launch_tile_prepare(int dtype, bool has_val, const LzArgs& a, int t0, int count, hipStream_t s);
 hipError_t launch_spmv_tile(int dtype, bool has_val, int j, const LzArgs& a, hipStream_t s);
-// Step 0's product from the all-ones start once more, as the preparation of a weighted graph wrote it.
-hipError_t launch_tile_first(int dtype, const LzArgs& a, hipStream_t s);
+// Step 0's product of the long rows of weighted graphs.
+hipError_t launch_tile_hub_first(int dtype, const LzArgs& a, hipStream_t s);
 
 // ---- launchers (k_tridiag.hip)
 // mode 0: final (closes step m_steps-1 when still open; writes y/theta/est, diag, checkpoint);

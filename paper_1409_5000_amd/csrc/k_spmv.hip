@@ -378,7 +378,9 @@ __global__ __launch_bounds__(kStagedThreads) void k_spmv_staged(LzArgs a, int j)
 // With values: 1024 threads and 32 KB chunks of values, a chunk at most one round of eight
 // coalesced loads per thread. Pattern-only: 256 threads (row pointers only; fewer waves to launch).
 __host__ __device__ constexpr int first_threads(bool has_val) { return has_val ? 1024 : kBlock; }
-template <typename T, bool HAS_VAL>
+// SHORT: but for the paneled form's long rows (a Barabasi-Albert graph's first row block, walked by one workgroup, took
+// 7.8 of n=1e6, degree 16, FP64's 7.9 ms).
+template <typename T, bool HAS_VAL, bool SHORT = false>
 __global__ __launch_bounds__(first_threads(HAS_VAL)) void k_spmv_first(LzArgs a) {
   constexpr int NT = first_threads(HAS_VAL), CAP = 32768 / (int)sizeof(T), U = kStreamU;
   __shared__ double chunks[kMaxChunks];
@@ -396,13 +398,14 @@ __global__ __launch_bounds__(first_threads(HAS_VAL)) void k_spmv_first(LzArgs a)
     for (int r = tid; r < rows; r += NT) w[r] = (T)((double)(rp[r + 1] - rp[r]) * sj);
   } else {
     const T* va = (const T*)a.values + tk.nnz_off;
+    const int hub = SHORT ? tile_hub<T>(n, rp[n - r0]) : 0;
     for (int i = tid; i <= rows; i += NT) rp_lds[i] = rp[i];
     __syncthreads();
     int ra = 0;
     while (ra < rows) {
       const int k0 = rp_lds[ra];
       if (rp_lds[ra + 1] - k0 > CAP) {  // one long row: thread 0 sums it in order
-        if (tid == 0) {
+        if (!SHORT && tid == 0) {
           double acc = 0.0;
           for (int k = k0; k < rp_lds[ra + 1]; ++k) acc += (double)va[k];
           w[ra] = (T)(acc * sj);
@@ -426,6 +429,7 @@ __global__ __launch_bounds__(first_threads(HAS_VAL)) void k_spmv_first(LzArgs a)
       }
       __syncthreads();
       for (int r = ra + tid; r < rb; r += NT) {
+        if (SHORT && rp_lds[r + 1] - rp_lds[r] > hub) continue;
         double acc = 0.0;
         for (int k = rp_lds[r] - k0; k < rp_lds[r + 1] - k0; ++k) acc += (double)lv[k];
         w[r] = (T)(acc * sj);
@@ -1405,6 +1409,13 @@ hipError_t launch_seg_prepare(int dtype, bool has_val, const LzArgs& a, int64_t 
 int staged_max_seglen(int dtype) {
   return dtype == EBTC_F64 ? (int)((kLdsBytes - staged_static_bytes<double>()) / 8)
                            : (int)((kLdsBytes - staged_static_bytes<float>()) / 4);
+}
+
+hipError_t launch_first_short(int dtype, const LzArgs& a, int64_t nb, hipStream_t s) {
+  const dim3 g((unsigned)nb), b(first_threads(true));
+  if (dtype == EBTC_F64) hipLaunchKernelGGL((k_spmv_first<double, true, true>), g, b, 0, s, a);
+  else hipLaunchKernelGGL((k_spmv_first<float, true, true>), g, b, 0, s, a);
+  return hipGetLastError();
 }
 
 hipError_t launch_spmv_step(int dtype, bool has_val, int lanes, int j, const LzArgs& a, int64_t nb, hipStream_t s) {

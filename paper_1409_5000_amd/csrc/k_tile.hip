@@ -53,13 +53,6 @@ struct TileShape {
   static constexpr int UL = COLS * (int)sizeof(T) / 16 / (kTileLoaders * 64);  // 16-byte loads per loader lane
 };
 
-// Rows with more entries are summed apart: than kTileHubMin and six times the realization's mean, or than the stream
-// form's capacity, beyond which that form's sums are not in entry order.
-constexpr int kTileHubMin = 256;
-template <typename T>
-__device__ inline int tile_hub(int64_t n, int64_t z) {
-  return (int)max((int64_t)kTileHubMin, min((int64_t)StreamShape<T>::CAP, 6 * z / max(n, (int64_t)1)));
-}
 
 // word of an entry: column in the panel << 2 (13 bits), row in the band << 16 (10 bits), rank << 26
 __device__ inline uint32_t tile_word(int col, int row, int rank) {
@@ -907,11 +900,7 @@ hipError_t launch_tile_prepare(int dtype, bool has_val, const LzArgs& a, int t0,
   return has_val ? tile_prepare_t<float, true>(a, t0, count, s) : tile_prepare_t<float, false>(a, t0, count, s);
 }
 
-// The product with the ones gives every row's values in entry order, as the sort sums them, but for rows beyond the
-// stream form's capacity, which k_tile_hub_first writes again with the other long rows.
-hipError_t launch_tile_first(int dtype, const LzArgs& a, hipStream_t s) {
-  const hipError_t e = launch_spmv_tile(dtype, true, 0, a, s);
-  if (e != hipSuccess) return e;
+hipError_t launch_tile_hub_first(int dtype, const LzArgs& a, hipStream_t s) {
   return dtype == EBTC_F64 ? hub_first_t<double>(a, s) : hub_first_t<float>(a, s);
 }
 

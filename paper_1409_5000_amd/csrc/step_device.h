@@ -45,6 +45,14 @@ struct StreamShape {
   static constexpr int CAP = sizeof(T) == 8 ? 3072 : 6144;  // product slots (24 KB)
 };
 
+// Paneled form: rows with more entries are summed apart: than kTileHubMin and six times the realization's mean, or than
+// the stream form's capacity, beyond which that form's sums are not in entry order.
+constexpr int kTileHubMin = 256;
+template <typename T>
+__device__ inline int tile_hub(int64_t n, int64_t z) {
+  return (int)max((int64_t)kTileHubMin, min((int64_t)StreamShape<T>::CAP, 6 * z / max(n, (int64_t)1)));
+}
+
 // SEQ_HUB: a row beyond the capacity is summed by one thread in entry order instead (the first
 // product's arithmetic, for a caller that must reproduce it).
 // RP_LDS: rp_lds already holds the rows' pointers (rp unused). NT_LOADS: the entries are read with the
