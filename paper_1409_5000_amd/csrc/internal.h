@@ -84,7 +84,7 @@ struct TileShare {
   int32_t n;        // order of the realization
   int32_t nblk;     // Task::nblk of the realization
   int32_t flag;     // kTileFlag*
-  int32_t pad;
+  int32_t hub;      // rows with more entries are summed apart
   int64_t vec_off, w_off, rowptr_off, part_off;  // Task's, w_off moved to the share's first row
 };
 struct TileCut {

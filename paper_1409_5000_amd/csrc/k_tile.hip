@@ -237,9 +237,8 @@ __global__ __launch_bounds__(kBlock) void k_tile_fill(LzArgs a, int t0, int coun
 // early second one, so that even the groups where classes meet seldom hold a row twice. Adds per group for 64 x
 // n=1e5, degree 20: 1.23 (first come, first placed: 1.90); n=4e5, degree 24: 1.17 (2.44).
 // Reads the columns twice and the values once, writes words and values: 20 bytes per weighted entry.
-// p0: the launch's first place.
 template <typename T, bool HAS_VAL>
-__global__ __launch_bounds__(kSortThreads) void k_tile_sort(LzArgs a, int p0) {
+__global__ __launch_bounds__(kSortThreads) void k_tile_sort(LzArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr int NT = kSortThreads, U = 8, K = kTileClasses;
   // the count's groups of 64 entries overlap by the K - 1 that decide their first entries' classes
@@ -250,7 +249,7 @@ __global__ __launch_bounds__(kSortThreads) void k_tile_sort(LzArgs a, int p0) {
   __shared__ int s_first[NT], s_len[NT];
   __shared__ int s_bad;
   // eight places, one per XCD, then their next bands
-  const int band = (blockIdx.x >> 3) % kTileBands, sh = p0 + (blockIdx.x >> 3) / kTileBands * 8 + (blockIdx.x & 7);
+  const int band = (blockIdx.x >> 3) % kTileBands, sh = (blockIdx.x >> 3) / kTileBands * 8 + (blockIdx.x & 7);
   const TileShare share = a.tile_share[sh];
   if (share.task < 0) return;
   const int tid = threadIdx.x, lane = tid & 63, w0r = tid - lane;  // w0r: the wave's first row slot
@@ -270,6 +269,7 @@ __global__ __launch_bounds__(kSortThreads) void k_tile_sort(LzArgs a, int p0) {
   const unsigned long long below = (1ull << lane) - 1ull;
   for (int i = tid; i < K * P; i += NT) next[i] = 0;
   if (tid == 0) s_bad = 0;
+  if (tid == 0 && band == 0) a.tile_share[sh].hub = hub;
   __syncthreads();
   bool bad = false;
   // adds (sign) the entries of lanes H to 63 to their panels and classes; top: a row's first entry
@@ -602,9 +602,9 @@ constexpr int kTileStream = 2;  // non-temporal: the matrix is read once per pro
 // 64 KB in flight per compute unit; measured at D U = 8, 16 and 18: 308, 226 and 209 us at n=1e5 x 64).
 // Short runs take short chunks: every chunk issues U loads, however few entries it holds (one graph of
 // n=1e6: 80 us with U = 2 against 103 with U = 6). All of a share's first loads wait on its record alone; the
-// step is opened from partials loaded with them and summed after the last panel. p0: the launch's first place.
+// step is opened from partials loaded with them and summed after the last panel.
 template <typename T, bool HAS_VAL, int U, int D>
-__global__ __launch_bounds__(kTileThreads) void k_spmv_tile(LzArgs a, int j, int p0) {
+__global__ __launch_bounds__(kTileThreads) void k_spmv_tile(LzArgs a, int j) {
   if (all_stopped(a, j)) return;
   constexpr int COLS = TileShape<T>::COLS, UL = TileShape<T>::UL, NT = kTileThreads;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -618,7 +618,6 @@ __global__ __launch_bounds__(kTileThreads) void k_spmv_tile(LzArgs a, int j, int
   static_assert(TileShape<T>::HCAP * sizeof(T) + NT / 64 * 8 + (kStreamRows + 1) * 4 <=
                     2 * COLS * sizeof(T) + sizeof(double) * kTileMaxRows, "scratch within the dynamic LDS");
   if (blockIdx.x < kTileHubGroups) {
-    if (p0 > 0) return;  // taken by the first of several launches
     for (int i = blockIdx.x; i < a.tile_count[2]; i += kTileHubGroups) {
       const HubBatch hb = a.hub_batch[i];
       const Task tk = a.tasks[hb.task];
@@ -628,7 +627,7 @@ __global__ __launch_bounds__(kTileThreads) void k_spmv_tile(LzArgs a, int j, int
     }
     return;
   }
-  const int sh = p0 + blockIdx.x - kTileHubGroups;
+  const int sh = blockIdx.x - kTileHubGroups;
   const TileShare share = a.tile_share[sh];
   const int task = uniform(share.task);
   if (task < 0) return;
@@ -794,8 +793,7 @@ __global__ __launch_bounds__(kTileThreads) void k_spmv_tile(LzArgs a, int j, int
   __syncthreads();
   if (!open(&sj)) return;
   if (flag & kTileFlagHubs) {  // the long rows are written by their own workgroups
-    const int32_t* rp0 = a.row_ptr + uniform(share.rowptr_off);
-    const int hub = tile_hub<T>(n, rp0[n]);
+    const int hub = a.tile_share[sh].hub;
     for (int i = tid; i < rows; i += NT)
       if (rp[i + 1] - rp[i] <= hub) w[i] = (T)(acc[i] * sj);
   } else {
@@ -836,9 +834,18 @@ hipError_t prepare_tile_t() {
 }
 
 // Places of one launch: a launch's threads number less than 2^32, so batches of some 350000 realizations and more sort
-// in several launches, and those of two million multiply in several.
+// in several launches, and those of two million multiply in several (each of which takes the long rows).
 constexpr int kSortPlaces = (int)(((int64_t)1 << 32) / (kTileBands * kSortThreads) / 8 * 8 - 8);
 constexpr int kTilePlaces = (int)((((int64_t)1 << 32) / kTileThreads - kTileHubGroups) / 8 * 8 - 8);
+
+// The arguments of a launch that starts at place p0.
+LzArgs from_place(const LzArgs& a, int p0) {
+  LzArgs p = a;
+  p.tile_share += p0;
+  p.tile_base += (int64_t)p0 * kTileBands;
+  p.tile_end += (int64_t)p0 * kTileBands * a.pan_pmax;
+  return p;
+}
 
 template <typename T>
 hipError_t hub_first_t(const LzArgs& a, hipStream_t s) {
@@ -858,7 +865,7 @@ hipError_t tile_prepare_t(const LzArgs& a, int t0, int count, hipStream_t s) {
                      places);
   for (int p0 = 0; p0 < places; p0 += kSortPlaces)
     hipLaunchKernelGGL((k_tile_sort<T, HAS_VAL>), dim3((unsigned)(std::min(places - p0, kSortPlaces) * kTileBands)),
-                       dim3(kSortThreads), sort_lds(a.pan_pmax), s, a, p0);
+                       dim3(kSortThreads), sort_lds(a.pan_pmax), s, from_place(a, p0));
   if constexpr (HAS_VAL)
     if (a.first_in_prepare) return hub_first_t<T>(a, s);
   return hipGetLastError();
@@ -870,7 +877,7 @@ hipError_t spmv_tile_t(int j, const LzArgs& a, hipStream_t s) {
   return tile_kernel<T, HAS_VAL>(a.tile_short, [&](auto k) {
     for (int p0 = 0; p0 < places; p0 += kTilePlaces)
       hipLaunchKernelGGL(k, dim3((unsigned)(std::min(places - p0, kTilePlaces) + kTileHubGroups)), dim3(kTileThreads),
-                         tile_lds<T>(), s, a, j, p0);
+                         tile_lds<T>(), s, from_place(a, p0), j);
     return hipGetLastError();
   });
 }

@@ -137,16 +137,21 @@ __device__ inline void spmv_stream_rows(const int32_t* __restrict__ rp, const in
     __syncthreads();
     for (int r = ra + tid; r < rb; r += NT) {
       double acc = 0.0;  // FP64: sequential sums over long (BA hub) rows stay accurate
-      int k = (rp_lds[r] - nz0) * (int)sizeof(T);
-      const int e = (rp_lds[r + 1] - nz0) * (int)sizeof(T);
-      if (k < e) {
+      if constexpr (NT != kBlock) {
+        const int e = rp_lds[r + 1] - nz0;
+        for (int k = rp_lds[r] - nz0; k < e; ++k) acc += (double)prod[k];
+      } else {
         // The loop within one 64-byte line of instructions: across two, a long row's chain takes up to 13% more time
         // (entry-balanced form, n=1e6 Barabasi-Albert, FP64: 0.241 and 0.275 ms a product).
-        asm volatile(".p2align 6" : "+v"(k), "+v"(acc));
-        do {
-          acc += (double)*(const T*)((const char*)prod + k);
-          k += (int)sizeof(T);
-        } while (k < e);
+        int k = (rp_lds[r] - nz0) * (int)sizeof(T);
+        const int e = (rp_lds[r + 1] - nz0) * (int)sizeof(T);
+        if (k < e) {
+          asm volatile(".p2align 6" : "+v"(k), "+v"(acc));
+          do {
+            acc += (double)*(const T*)((const char*)prod + k);
+            k += (int)sizeof(T);
+          } while (k < e);
+        }
       }
       w_out[r] = (T)(acc * scale);
     }
