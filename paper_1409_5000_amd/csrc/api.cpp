@@ -919,7 +919,11 @@ int run_pass2(const ebtc_batch* b, const ebtc_opts* o, const LzArgs& a1, const s
       if (x.nb == 0) continue;
       // the second pass never skips step 0: the sort's product of the first pass is gone
       if (j == 0 && x.sp.form == EBTC_SPMV_PANELED && x.a.first_in_prepare) {  // the long rows as the sort does them
-        EBTC_PHASE(prof, EBTC_PHASE_FIRST, launch_first_short(b->dtype, x.a, x.nb, s));
+        // Rows of many entries come from the tiles: the row sums take one thread for each. FP64, 16 x n=100000: 24
+        // entries per row 118 us from the CSR and 110 from the tiles, 12: 60 and 72; 40 x n=20000, 100: 375 and 174;
+        // 10 x n=8000, 1600: 62.7 ms and 0.36; against it 2 x n=1e6, 40: 0.22 and 0.30.
+        if (b->mean_degree >= 32.0) EBTC_PHASE(prof, EBTC_PHASE_FIRST, launch_spmv_tile(b->dtype, has_val, 0, x.a, s));
+        else EBTC_PHASE(prof, EBTC_PHASE_FIRST, launch_first_short(b->dtype, x.a, x.nb, s));
         EBTC_PHASE(prof, EBTC_PHASE_FIRST, launch_tile_hub_first(b->dtype, x.a, s));
         continue;
       }

@@ -256,6 +256,27 @@ def test_second_pass_of_the_memory_bounded_form(gpu_lib, dtype):
             assert same, kw
 
 
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("degree", [20, 48])
+def test_second_pass_on_rows_of_many_entries(gpu_lib, dtype, degree):
+    # the sorted entries give the second pass's step 0 from a mean of 32 entries per row on, the CSR below; columns out
+    # of order in one realization, long rows on both sides of the stream form's capacity
+    n = 17_000
+    rng = np.random.default_rng(53)
+    lengths = rng.integers(degree - 8, degree + 8, n)
+    lengths[[0, 9, 10, 8000, 16999]] = [400, 3072, 3073, 6200, 9000]
+    rp = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    ci = np.concatenate([np.sort(rng.choice(n, k, replace=False)) for k in lengths]).astype(np.int32)
+    va = rng.uniform(0.1, 1.0, rp[-1])
+    k = int(rp[12_000])
+    ci2, va2 = ci.copy(), va.copy()
+    ci2[[k, k + 1]], va2[[k, k + 1]] = ci[[k + 1, k]], va[[k + 1, k]]
+    b = api().Batch.from_csr([[(rp, ci, va), (rp, ci2, va2)]], dtype=dtype)
+    for kw in (dict(m=6, reorth=0), dict(m=6, reorth=0, schedule="plain")):
+        same = scored(b, spmv="paneled", **kw) == scored(b, spmv="stream", **kw)
+        assert same, kw
+
+
 @pytest.mark.parametrize("dtype,degree,long_row", [("f64", 620, 3500), ("f32", 1200, 6500)])
 def test_rows_beyond_the_capacity_of_a_dense_graph(gpu_lib, dtype, degree, long_row):
     # six times the mean passes the stream form's capacity here: rows between the two are long rows all the same (the
