@@ -109,3 +109,12 @@ def test_dense_graphs_stay_on_the_schedule_of_launches(gpu_lib, dtype, n, entrie
     run = b.run(m=0)
     run.launch()
     assert run.profile()["solve"][1] == 0
+
+
+@pytest.mark.parametrize("kw,solves", [(dict(m=1), 0), (dict(m=0, m_max=1), 0), (dict(m=2), 1)])
+def test_one_step_of_a_pattern_stays_on_the_schedule_of_launches(gpu_lib, kw, solves):
+    # one step of a pattern-only graph needs its degrees alone: no product that the workgroup's solve could save on
+    b = api().generated_batch([dict(family="ba", n=5000, count=100, seed=3, k=4)], dtype="f64")
+    run = b.run(**kw)
+    run.launch()
+    assert run.profile()["solve"][1] == solves
