@@ -142,8 +142,9 @@ enum ebtc_spmv_form {
                                 6144 FP64; the kernels take at most 8192 / 4096); each step then stages
                                 one panel's vector slice at a time in LDS, gathers from it and adds
                                 every product to its row's sum in entry order (the stream form's sums,
-                                bit for bit). Long rows (more than 256 entries and six times the mean)
-                                are summed apart; a share with columns out of order uses the CSR-stream
+                                bit for bit). Long rows (more than 256 entries and six times the mean,
+                                or more than the stream form holds in LDS: 6144 FP32 / 3072 FP64) are
+                                summed apart; a share with columns out of order uses the CSR-stream
                                 arithmetic; at most 1024 panels of the columns asked for per
                                 realization                                                          */
 };

@@ -7,8 +7,9 @@
 // One launch replaces the per-phase sequence start, [SpMV, Gram-Schmidt dots and update, adaptive
 // check] x m, small exponential, basis combination: workgroup barriers take the place of kernel
 // boundaries, and the realization's working set stays in LDS -- the state, the partial sums, the row
-// pointers, the gathered vector v_j and the product w always; the basis and the CSR entries when they
-// fit the launch's LDS budget (the host decides per launch), else the workspace and the input arrays.
+// pointers, the gathered vector v_j and the product w always; the CSR entries where they fit, and the
+// basis where it fits beside them and costs no round of workgroups (solve_lds, per launch), else the input
+// arrays and the workspace.
 // Every phase keeps the per-phase kernels' arithmetic in their thread order: the CSR-stream SpMV's (which the
 // column-segmented and entry-balanced forms share bit for bit), the dot partials of the dot kernel the window would
 // get (1024 or 256 threads; a partial's bits do not depend on how many vectors one pass covers, so they are formed

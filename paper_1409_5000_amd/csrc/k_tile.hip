@@ -5,8 +5,8 @@
 // to 8192 FP32 / 4096 FP64 elements, 32 KB): the rows' FP64 sums stay in LDS for a whole product, the
 // panels' vector slices pass through two LDS buffers, and an entry costs one LDS read (the gather) and one
 // LDS add (its row's sum). Once per call the entries are put in that order:
-//   cut    a realization's rows into shares of at most tile_rows rows and about three times the mean
-//          share's entries (k_tile_cut, k_tile_pack, k_tile_fill: a dense list of the shares of the launch);
+//   cut    a realization's rows into shares of at most tile_rows rows and a quarter more entries than the
+//          mean share's (k_tile_cut, k_tile_pack, k_tile_fill: a dense list of the shares of the launch);
 //   sort   each share's rows are cut into kTileBands equal bands, one per wave of the product. A band's
 //          entries, panel by panel, replace its CSR range (k_tile_sort): one word per entry (column in the
 //          panel, row in the band, rank) and its value.
@@ -15,8 +15,8 @@
 // instruction, where the order of the adds is not defined: the sort places the rows' first entries of a panel
 // before the second ones and so on (kTileClasses), so that they seldom do, and where they do the entry's rank
 // (the number of its row's earlier entries in its group of 64) puts it in a later add.
-// Long rows (kTileHubMin) would fill whole groups, one add per entry; they are listed apart and
-// summed by workgroups of their own in the same launch from products staged in LDS, one thread per row.
+// Long rows (tile_hub) would fill whole groups, one add per entry; they are listed apart and summed by
+// workgroups of their own in the same launch from products staged in LDS, one thread per row.
 //
 // Bound by the entry stream and, for few entries per tile, by the slices. Per product, FP32 (us; before: the
 // fastest other form):
@@ -52,7 +52,6 @@ struct TileShape {
   static constexpr int HCAP = 128 * 1024 / sizeof(T);         // products of a batch of long rows
   static constexpr int UL = COLS * (int)sizeof(T) / 16 / (kTileLoaders * 64);  // 16-byte loads per loader lane
 };
-
 
 // word of an entry: column in the panel << 2 (13 bits), row in the band << 16 (10 bits), rank << 26
 __device__ inline uint32_t tile_word(int col, int row, int rank) {
@@ -142,9 +141,9 @@ __global__ __launch_bounds__(64) void k_tile_cut(LzArgs a, int t0, int again) {
 // again = 1: the realizations' share counts to offsets in the launch. Before that the rows per share: where
 // shares end early they come on top of the rounds of kTileUnits that the host filled, and a few shares over
 // would cost a whole round, so every share takes more rows, or, at the most a unit holds, one round more is
-// filled, and never fewer rows than the host sized the slots for (8 x n=436472 Barabasi-Albert: 560 shares of 6821 rows took 3 rounds, 316 us a product; two rounds now,
+// filled (8 x n=436472 Barabasi-Albert: 560 shares of 6821 rows took 3 rounds, 316 us a product; two rounds now,
 // 194 us). 15% to spare: such graphs have shares of few, long rows, which take longer (three n=1e6 graphs:
-// 224 us a product with 6%, 209 with 15, 215 with 25).
+// 224 us a product with 6%, 209 with 15, 215 with 25). Never fewer rows than the host sized the slots for.
 __global__ __launch_bounds__(1024) void k_tile_pack(LzArgs a, int t0, int count, int again) {
   __shared__ int wsum[16];
   __shared__ double su[16], sf[16];
