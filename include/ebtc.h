@@ -55,7 +55,8 @@ enum ebtc_schedule {
                               and an update launch (dots and update are one launch when every
                               realization has at most 2048 nodes), plus a few per realization. A
                               recorded paneled form (ebtc_tune) gives way to the entry-balanced
-                              one, whose results are the same bits                                 */
+                              one, whose results are the same bits (under every schedule so for one
+                              step of a batch without values, which has no product)                */
   EBTC_SCHED_BATCHED = 2,  /* all realizations of all graphs advance together, one launch per
                               Lanczos phase, optionally replayed from a captured hipGraph          */
   EBTC_SCHED_SINGLE = 3    /* all realizations in one launch, one workgroup running each

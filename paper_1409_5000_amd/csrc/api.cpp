@@ -590,9 +590,12 @@ BatchPlan balanced_plan(const ebtc_batch* b, const ebtc_opts* o) {
 // The plan of a forward call. The tuner times launches over the whole batch. Under the plain schedule a launch covers
 // one realization: its tiles leave compute units idle and their preparation is launches of its own, so the
 // entry-balanced form runs instead (16 x ER n=1e5, degree 20: 34.1 ms paneled, 15.6 balanced; 2 x n=1e6: 7.7 and 6.6;
-// the other way round on Barabasi-Albert graphs, 8 x n=1e5: 16.6 and 32.8, which one cannot tell here).
+// the other way round on Barabasi-Albert graphs, 8 x n=1e5: 16.6 and 32.8, which one cannot tell here). So it does for
+// one step of a pattern-only batch, which has no product to prepare for (16 x ER n=1e5, degree 20, FP64: 318 us paneled,
+// 109 balanced).
 BatchPlan call_plan(const ebtc_batch* b, const ebtc_opts* o) {
-  return o->schedule == EBTC_SCHED_PLAIN ? balanced_plan(b, o) : spmv_plan(b, o);
+  const bool no_product = (o->m > 0 ? o->m : o->m_max) == 1 && !b->values;
+  return o->schedule == EBTC_SCHED_PLAIN || no_product ? balanced_plan(b, o) : spmv_plan(b, o);
 }
 
 LzArgs make_args(const ebtc_batch* b, const ebtc_opts* o, char* ws, const Layout& L) {
@@ -1348,7 +1351,7 @@ int ebtc_profile_phases(ebtc_batch* b, const ebtc_opts* o, void* ws, size_t ws_b
   int rc = check_opts(o);
   if (rc) return rc;
   if (!ws || !scores_out || !log_scale_out) return fail(EBTC_EINVAL, "NULL workspace, scores or log_scale output");
-  const BatchPlan bp = spmv_plan(b, o);
+  const BatchPlan bp = o->schedule == EBTC_SCHED_PLAIN ? spmv_plan(b, o) : call_plan(b, o);  // never the plain loop
   rc = check_plan(b, bp);
   if (rc) return rc;
   const Layout L = make_layout(b, o, bp);

@@ -203,6 +203,23 @@ def test_recorded_form_in_the_fixed_array(gpu_lib):
         b.scores_noalloc(m=5, spmv="paneled")  # by name: as asked
 
 
+@pytest.mark.parametrize("kw", [dict(m=1), dict(m=0, m_max=1), dict(m=1, reorth=0)])
+def test_one_step_of_a_pattern_is_not_prepared_for(gpu_lib, kw):
+    # it has no product: a recorded paneled form gives way to the balanced one, whose workspace is then enough
+    n = 60_000
+    rng = np.random.default_rng(59)
+    b = api().Batch.from_csr([[csr(n, G.er_keys(n, 12.0 / (n - 1), rng), rng, False)]], dtype="f64")
+    ref = scored(b, spmv="stream", **kw)
+    need = b.run(spmv="balanced", **kw).ws_bytes
+    assert need < b.run(spmv="paneled", **kw).ws_bytes
+    b.set_forms(["paneled"])
+    run = b.run(hipgraph=False, **kw)
+    run.ws_bytes = need
+    out = run.launch()
+    same = (out.scores.cpu().numpy().tobytes(), out.log_scale.cpu().numpy().tobytes(), out.diag_numpy().tobytes()) == ref
+    assert same
+
+
 @pytest.mark.parametrize("n,R,weighted", [(40, 400_000, True), (6, 2_097_100, False)])
 def test_more_places_than_one_launch_takes(gpu_lib, n, R, weighted):
     # two share slots a realization, twelve workgroups of 512 threads each in the sort (less than 2^32 threads a launch:
