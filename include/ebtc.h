@@ -203,9 +203,9 @@ int ebtc_scores(ebtc_batch* batch, const ebtc_opts* opts, void* ws, size_t ws_by
  * is looked up once per GPU on the first call there. Arguments, outputs, results and errors as for
  * ebtc_scores, plus EBTC_EWORKSPACE when ebtc_plan's size for (batch, opts) exceeds the array (nothing
  * is enqueued then). Where that is the size of a recorded paneled form (ebtc_tune) and the
- * entry-balanced one fits, that one runs. Every call on one GPU uses that GPU's one array: calls that overlap on a GPU
- * (other threads, other streams, or a second call enqueued before the first has run on another
- * stream) race and give undefined results; calls in order on one stream do not. */
+ * entry-balanced one fits, that one runs. Every call on one GPU uses that GPU's one array: calls that
+ * overlap on a GPU (other threads, other streams, or a second call enqueued before the first has run on
+ * another stream) race and give undefined results; calls in order on one stream do not. */
 #define EBTC_NOALLOC_WS_BYTES ((size_t)64 << 20)
 int ebtc_scores_noalloc(ebtc_batch* batch, const ebtc_opts* opts, void* scores_out, double* log_scale_out,
                         void* ckpt_out, ebtc_diag* diag_out, void* stream);
